@@ -282,8 +282,14 @@ int run_kick(const vlasov_grid* g, const Dims& d, int prec, int vbc, const void*
 {
     if (!isfinite(dt)) return VLASOV_ERR_NONFINITE;
     int nu[3] = {(int)d.nu[0], (int)d.nu[1], (int)d.nu[2]};
-    const bool yz64 = kick_yz64_supported(nu, lds_limit());
-    if (kick_supported(nu, lds_limit()) || yz64) {
+    const size_t lim = lds_limit();
+    const bool yz64 = kick_yz64_supported(nu, lim);
+    const bool cube = kick_supported(nu, lim);
+    // any other block that fits LDS whole: one pass over f instead of three
+    // (FP32, 20 x 18 x 15 cells of 24 x 20 x 18: 0.94 -> 0.19 ms per kick;
+    // 8^3 cells of 8^3, launches and latency: 30 -> 11 us)
+    const bool any = !cube && !yz64 && kick_any_supported(prec, nu, lim);
+    if (cube || yz64 || any) {
         KickArgs a;
         memset(&a, 0, sizeof(a));
         a.g = field;
@@ -302,6 +308,11 @@ int run_kick(const vlasov_grid* g, const Dims& d, int prec, int vbc, const void*
         for (int k = 0; k < 3; ++k) {
             a.umin[k] = -g->umax[k];
             a.du[k] = 2.0 * g->umax[k] / g->nu[k];
+        }
+        if (any) {
+            const int rc = from_hip(launch_kick_any(prec, fin, sin, fout, sout, a, st));
+            if (rc || rho == nullptr) return rc;
+            return run_moments(g, d, prec, fout, sout, rho, umean, nullptr, st);
         }
         if (!yz64) return from_hip(launch_kick(prec, fin, sin, fout, sout, a, shifts, st));
         // 64^3 blocks: ux on its own, then uy and uz fused on slabs of the

@@ -94,6 +94,12 @@ bool kick_yz64_supported(const int nu[3], size_t lds_limit);
 hipError_t launch_kick_yz64(int prec, const void* fin, const float* sin, void* fout, float* sout,
                             const KickArgs& a, KickShift* shifts, hipStream_t st);
 
+// other block shapes that fit LDS (kick_any.hip); the bits of the three single
+// sweeps in every storage form
+bool kick_any_supported(int prec, const int nu[3], size_t lds_limit);
+hipError_t launch_kick_any(int prec, const void* fin, const float* sin, void* fout, float* sout,
+                           const KickArgs& a, hipStream_t st);
+
 struct MomArgs {
     long cells;
     long Nu;
@@ -126,6 +132,7 @@ struct FieldArgs {
 };
 inline size_t field_align(size_t b) { return (b + 255) & ~(size_t)255; }
 // workspace: three twiddle tables, two complex [cells] buffers, three more
+// (the direct sums' need; the half-spectrum transforms use less)
 inline size_t field_workspace_bytes(const int n[3])
 {
     const size_t cells = (size_t)n[0] * n[1] * n[2];
