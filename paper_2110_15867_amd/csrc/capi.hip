@@ -143,6 +143,10 @@ int make_pos_args(const vlasov_grid* g, const Dims& d, int axis, double dt_over_
     a.nuz = d.nu[2];
     a.nux = d.nu[0];
     a.V = axis == 2 ? 1 : vector_width(d.nu[2]);
+    // small grids: with V lines per thread there is less than one wave for
+    // each of the chip's 1024 SIMDs, and a wave's walk is V times as long
+    // (8^3 cells of 8^3: 128 waves and 16 us per x sweep; 512 and 6.5 us)
+    if (a.O * a.I < 1024L * 64 * a.V) a.V = 1;
     a.G = (int)(d.nu[2] / a.V);
     for (long j = 0; j < d.nu[axis]; ++j) {
         a.shift[j] = position_shift(g, axis, j, dt_over_a2);

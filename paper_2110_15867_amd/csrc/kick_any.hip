@@ -21,7 +21,6 @@
 // them.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-#include <type_traits>
 
 #include "launch.hpp"
 #include "rows.hpp"
@@ -77,18 +76,18 @@ __device__ __forceinline__ float sweep_line(float* x, int step, int M, const Lin
         dm2 = dm1; dm1 = d0; d0 = dp1;
         D0 = Dp; Mm = Mp;
     };
-    int j = 0;
 #pragma unroll 1
-    for (; j + 6 <= M; j += 4) {
+    for (int j0 = 0; j0 < M; j0 += 4) {
         float n[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) n[q] = at(j + 2 + q);
+        for (int q = 0; q < 4; ++q) {
+            const int k = j0 + 2 + q;                 // (uniform)
+            n[q] = k < M ? at(k) : (k == M ? wrap0 : wrap1);
+        }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) cell(j + q, n[q]);
+        for (int q = 0; q < 4; ++q)
+            if (j0 + q < M) cell(j0 + q, n[q]);
     }
-#pragma unroll 1
-    for (; j < M; ++j)
-        cell(j, j + 2 < M ? at(j + 2) : (j + 2 == M ? wrap0 : wrap1));
     return phi_top;
 }
 
@@ -134,26 +133,27 @@ __device__ __forceinline__ float add_group(float acc, float a)
 }
 
 // One vacuum line swept and translated; returns the content its group of G
-// lines (consecutive lanes) lets out, in every lane: a single sweep walks G
-// lines per thread with one FP32 sum over them, row by row -- the rows past
-// the upper face, the flux through it, then any rows further out -- and this
-// adds the same values in the same order.  (For shifts of three cells and
-// more the rows further out are summed before the flux: the walk in place
-// has overwritten them by then.)
+// lines (consecutive lanes; with `one`, its own) lets out, in every lane: a
+// single sweep of ux or uy walks G lines per thread with one FP32 sum over
+// them, row by row -- the rows past the upper face, the flux through it, then
+// any rows further out -- and this adds the same values in the same order.
+// (For shifts of three cells and more the rows further out are summed before
+// the flux: the walk in place has overwritten them by then.)
 template <int G>
-__device__ __forceinline__ float vacuum_line(float* x, int step, int M, const LineShift& sh)
+__device__ __forceinline__ float vacuum_line(float* x, int step, int M, const LineShift& sh, bool one)
 {
+    auto add = [&](float s, float v) { return one ? s + v : add_group<G>(s, v); };
     const int N = sh.N;
     float acc = 0.0f, far = 0.0f;
     if (N > 0) {
         for (int p = (M - N > 0 ? M - N : 0); p < M; ++p) {
             const float v = x[p * step];
-            if (p < M - N + 2) acc = add_group<G>(acc, v);
-            else far = add_group<G>(far, v);
+            if (p < M - N + 2) acc = add(acc, v);
+            else far = add(far, v);
         }
     }
     const float phi = sweep_line<false>(x, step, M, sh, M - 1 - N);
-    acc = add_group<G>(acc, N <= M ? phi : 0.0f);
+    acc = add(acc, N <= M ? phi : 0.0f);
     if (N > 0) {
         acc += far;
         shift_line<false>(x, step, M, N);
@@ -188,7 +188,7 @@ __global__ void __launch_bounds__(1024) k_kick_any(const typename Codec<P>::T* _
     using T = typename Codec<P>::T;
     extern __shared__ float lds[];
     __shared__ LineShift shifts[3];
-    __shared__ double red[16];
+    __shared__ double red[3][16];
     const long cell = blockIdx.x;
     const int nz = b.nu[2], lz = b.lz;
     const int nlz = b.nu[0] * b.nu[1];              // uz-lines
@@ -196,6 +196,9 @@ __global__ void __launch_bounds__(1024) k_kick_any(const typename Codec<P>::T* _
     float* lmax = lds + nlz * lz;                   // scale per uz-line (scaled storage)
     const T* src = fin + cell * nv;
     const float* ssrc = sin + cell * nlz;
+    // the cell's outflow total so far, needed only at the end
+    double prev = 0.0;
+    if (a.outflow != nullptr && !PER && threadIdx.x == 0) prev = a.outflow[cell];
 
     // the block into LDS; the three shift splits are made by one lane each
     // while the loads are in flight
@@ -232,32 +235,27 @@ __global__ void __launch_bounds__(1024) k_kick_any(const typename Codec<P>::T* _
                                               a.factor[threadIdx.x], b.nu[threadIdx.x], PER);
     __syncthreads();
 
-    double out[3];
-    auto sweep = [&](auto axis) {
-        constexpr int ax = decltype(axis)::value;
+    double out[3] = {0.0, 0.0, 0.0};
+#pragma unroll 1
+    for (int ax = 0; ax < 3; ++ax) {
         const LineShift sh = uniform_shift(shifts[ax]);
-        const int M = b.nu[ax];
+        const int M = uniform_sgpr(b.nu[ax]);
         // lines (o, k): k over jz (ux: also jy, as o) at stride S
         const int S = ax == 0 ? b.nu[1] * lz : (ax == 1 ? lz : 1);
+        const int os = ax == 0 ? lz : (ax == 1 ? b.nu[1] * lz : lz);
         const int nl = ax == 0 ? b.nu[1] * nz : (ax == 1 ? b.nu[0] * nz : nlz);
         const int step = sh.neg ? -S : S;
         double mine = 0.0;
         for (int l = threadIdx.x; l < nl; l += blockDim.x) {
-            int base;
-            if (ax == 2) {
-                base = l * lz;
-            } else {
-                const int o = b.dz.div(l);
-                base = (ax == 0 ? o * lz : o * b.nu[1] * lz) + (l - o * nz);
-            }
+            const int o = ax == 2 ? l : b.dz.div(l);
+            const int base = o * os + (ax == 2 ? 0 : l - o * nz);
             float* x = lds + base + (sh.neg ? (M - 1) * S : 0);
             if (PER) {
                 sweep_line<true>(x, step, M, sh, M - 1);
                 if (sh.N > 0) shift_line<true>(x, step, M, sh.N);
             } else {
-                constexpr int G = ax == 2 ? 1 : V;
-                const float ofl = vacuum_line<G>(x, step, M, sh);
-                if (G == 1 || threadIdx.x % G == 0) mine += (double)ofl;
+                const float ofl = vacuum_line<V>(x, step, M, sh, ax == 2);
+                if (ax == 2 || threadIdx.x % V == 0) mine += (double)ofl;
             }
             if (Codec<P>::scaled && ax == 2) {
                 float* z = lds + l * lz;
@@ -267,7 +265,9 @@ __global__ void __launch_bounds__(1024) k_kick_any(const typename Codec<P>::T* _
                 sout[cell * nlz + l] = m;
             }
         }
-        out[ax] = mine;
+        out[0] = ax == 0 ? mine : out[0];
+        out[1] = ax == 1 ? mine : out[1];
+        out[2] = ax == 2 ? mine : out[2];
         __syncthreads();
         if (Codec<P>::scaled && ax < 2) {
             // what a sweep stores and the next one loads: codes and back
@@ -280,10 +280,7 @@ __global__ void __launch_bounds__(1024) k_kick_any(const typename Codec<P>::T* _
             }
             __syncthreads();
         }
-    };
-    sweep(std::integral_constant<int, 0>{});
-    sweep(std::integral_constant<int, 1>{});
-    sweep(std::integral_constant<int, 2>{});
+    }
 
     T* dst = fout + cell * nv;
     for (int e = threadIdx.x * V; e < nv; e += blockDim.x * V) {
@@ -296,16 +293,23 @@ __global__ void __launch_bounds__(1024) k_kick_any(const typename Codec<P>::T* _
         *reinterpret_cast<Pack<T, V>*>(dst + e) = q;
     }
     if (a.outflow != nullptr && !PER) {
-        double acc = 0.0;
+        // the three axes' FP64 sums, over each wave and then in wave order
+        const int wave = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;
 #pragma unroll
         for (int ax = 0; ax < 3; ++ax) {
-            const double tot = block_sum(out[ax], red);
-            if (threadIdx.x == 0) {
-                if (ax == 0) acc = a.outflow[cell];
-                acc += tot * a.du3;
-            }
+            const double w = wave_sum_f64(out[ax]);
+            if ((threadIdx.x & 63) == 0) red[ax][wave] = w;
         }
-        if (threadIdx.x == 0) a.outflow[cell] = acc;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+#pragma unroll
+            for (int ax = 0; ax < 3; ++ax) {
+                double tot = 0.0;
+                for (int q = 0; q < nw; ++q) tot += red[ax][q];
+                prev += tot * a.du3;
+            }
+            a.outflow[cell] = prev;
+        }
     }
 }
 

@@ -440,6 +440,39 @@ struct ContigWriter {
     }
 };
 
+// A double moved between lanes by a DPP control (each 32-bit half).
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v)
+{
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const int lo = __builtin_amdgcn_update_dpp((int)u, (int)u, CTRL, 0xF, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp((int)(u >> 32), (int)(u >> 32), CTRL, 0xF, 0xF, false);
+    return __builtin_bit_cast(double, ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
+}
+
+__device__ __forceinline__ double read_lane_f64(double v, int lane)
+{
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = __builtin_amdgcn_readlane((int)u, lane);
+    const unsigned hi = __builtin_amdgcn_readlane((int)(u >> 32), lane);
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// The sum of v over the wave, the same in every lane: a DPP tree within each
+// 16-lane row (quad permutations, then half-row and row mirrors; partners
+// add the same two partial sums, so every lane of a row holds the same bits),
+// then the four row sums in row order.  Short VALU latencies: the sum sits
+// right before a barrier.
+__device__ __forceinline__ double wave_sum_f64(double v)
+{
+    v += dpp_f64<0xB1>(v);     // quad_perm [1,0,3,2]
+    v += dpp_f64<0x4E>(v);     // quad_perm [2,3,0,1]
+    v += dpp_f64<0x141>(v);    // row_half_mirror
+    v += dpp_f64<0x140>(v);    // row_mirror
+    return ((read_lane_f64(v, 0) + read_lane_f64(v, 16)) + read_lane_f64(v, 32)) +
+           read_lane_f64(v, 48);
+}
+
 // ---------------------------------------------------------------------------
 // FP64 reduction of one value per thread over the work-group, fixed order.
 // Returns the total in thread 0.

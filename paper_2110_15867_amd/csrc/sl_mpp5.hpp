@@ -411,17 +411,20 @@ __device__ __forceinline__ LineShift uniform_shift(const LineShift& sh)
 }
 
 // ---------------------------------------------------------------------------
-// Rows requested ahead of use.  With the line length known at compile time
-// a walk is fully unrolled, so the ring slot of every row is a constant and
-// the ring lives in registers: PD rows are in flight while the fluxes of
+// Rows requested ahead of use.  The ring of PD rows lives in registers, its
+// slots compile-time constants: PD rows are in flight while the fluxes of
 // earlier rows are computed (HBM needs many bytes in flight per CU, and one
-// row of one wave is only 256 B-1 KiB).  The walks read rows strictly in
-// order; take(i) hands out the i-th row of the walk's loop and requests row
-// i + PD, never beyond the L rows the loop consumes.
+// row of one wave is only 256 B-1 KiB).  With the line length known at
+// compile time a walk is fully unrolled; otherwise it is unrolled by the ring
+// (one row at a time, the walk of a short line is a chain of load latencies:
+// z of 20 x 18 x 15 cells of 24 x 20 x 18 took 132 us, 110 with four rows in
+// flight).  The walks read rows strictly in order; take(i) hands out the i-th
+// row of the walk's loop and requests row i + PD, never beyond the L rows the
+// loop consumes.
 // ---------------------------------------------------------------------------
 template <int V, int MT>
 struct RowPipeDepth {
-    static constexpr int value = MT == 0 ? 1 : (V >= 2 ? 4 : 8);
+    static constexpr int value = MT == 0 ? 4 : (V >= 2 ? 4 : 8);
 };
 
 template <int V, int PD, class Reader>
@@ -436,17 +439,129 @@ struct RowPipe {
         for (int q = 0; q < PD; ++q)
             if (q < L) rd.next(ring[q]);
     }
-    __device__ void take(int i, int L, float* x)
+    // slot = i % PD, a constant of the unrolled walk
+    __device__ void take(int i, int slot, int L, float* x)
     {
-        if (PD == 1) {
-            rd.next(x);
-            return;
-        }
 #pragma unroll
-        for (int v = 0; v < V; ++v) x[v] = ring[i % PD][v];
-        if (i + PD < L) rd.next(ring[i % PD]);
+        for (int v = 0; v < V; ++v) x[v] = ring[slot][v];
+        if (i + PD < L) rd.next(ring[slot]);
     }
 };
+
+// ---------------------------------------------------------------------------
+// walk_uniform (below) for a line length known at run time only.
+// ---------------------------------------------------------------------------
+template <int V, bool UNI, class Reader, class Writer>
+__device__ __forceinline__ void walk_uniform_any(Reader& rd, Writer& wr, const int M,
+                                             const LineShift& sh, const bool periodic,
+                                             float* ofl)
+{
+    const int N = sh.N;
+    float xm2[V], xm1[V], x0[V], xp1[V], xp2[V], phi_old[V];
+    float dm2[V], dm1[V], d0[V], dp1[V];    // x_{j-1}-x_{j-2}, ..., x_{j+2}-x_{j+1}
+    // curvature at j and d^M4 at j-1/2, carried (flux_mag_mm).  Carrying
+    // adds a minmod per interface outside the early-out test and saves two
+    // behind it: it pays where the test fails often.  Not for waves of single
+    // lines with per-lane shifts (one-direction waves of the z sweep), where
+    // it was measured to cost time.
+    constexpr bool CARRY = UNI || V > 1;
+    float cj[V], kj[V];
+    float acc = 0.0f;
+    int r = -N - 3;                       // frame row of the next value
+    rd.seek(r);
+    rd.next(xm2); rd.next(xm1); rd.next(x0); rd.next(xp1); rd.next(xp2);
+    constexpr int PD = RowPipeDepth<V, 0>::value;
+    RowPipe<V, PD, Reader> pipe(rd);
+    pipe.prime(M);
+    if (!periodic) {
+        // rows already in the window that lie past the upper face
+        auto past = [&](int row) { return row >= M - N && row < M; };
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            acc += past(r) ? xm2[v] : 0.0f;
+            acc += past(r + 1) ? xm1[v] : 0.0f;
+            acc += past(r + 2) ? x0[v] : 0.0f;
+            acc += past(r + 3) ? xp1[v] : 0.0f;
+            acc += past(r + 4) ? xp2[v] : 0.0f;
+        }
+    }
+    r += 5;
+    // flux through (j0-1)+1/2, j0 = -N; then slide the window to j0
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        dm2[v] = xm1[v] - xm2[v];
+        dm1[v] = x0[v] - xm1[v];
+        d0[v] = xp1[v] - x0[v];
+        dp1[v] = xp2[v] - xp1[v];
+        const Stencil st{xm2[v], xm1[v], x0[v], xp1[v], xp2[v], dm2[v], dm1[v], d0[v], dp1[v]};
+        if constexpr (CARRY) {
+            const float c0 = d0[v] - dm1[v], cp = dp1[v] - d0[v];
+            const float Mp = curv_minmod(c0, cp);
+            phi_old[v] = flux_mag_mm<UNI>(st, sh, curv_minmod(dm1[v] - dm2[v], c0), Mp);
+            cj[v] = cp;
+            kj[v] = Mp;
+        } else {
+            phi_old[v] = flux_mag<UNI>(st, sh);
+        }
+        xm2[v] = xm1[v]; xm1[v] = x0[v]; x0[v] = xp1[v]; xp1[v] = xp2[v];
+        dm2[v] = dm1[v]; dm1[v] = d0[v]; d0[v] = dp1[v];
+    }
+    // step i; slot = i % PD
+    auto step = [&](int i, int slot) __attribute__((always_inline)) {
+        // new row j+2 for j = i - N
+        pipe.take(i, slot, M, xp2);
+        if (!periodic) {
+            if (r >= M - N && r < M) {
+#pragma unroll
+                for (int v = 0; v < V; ++v) acc += xp2[v];
+            }
+        }
+        ++r;
+        float res[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            dp1[v] = xp2[v] - xp1[v];
+            const Stencil st{xm2[v], xm1[v], x0[v], xp1[v], xp2[v], dm2[v], dm1[v], d0[v], dp1[v]};
+            float phi;
+            if constexpr (CARRY) {
+                const float cp = dp1[v] - d0[v];
+                const float Mp = curv_minmod(cj[v], cp);
+                phi = flux_mag_mm<UNI>(st, sh, kj[v], Mp);
+                cj[v] = cp;
+                kj[v] = Mp;
+            } else {
+                phi = flux_mag<UNI>(st, sh);
+            }
+            res[v] = x0[v] - (phi - phi_old[v]);
+            phi_old[v] = phi;
+            xm2[v] = xm1[v]; xm1[v] = x0[v]; x0[v] = xp1[v]; xp1[v] = xp2[v];
+            dm2[v] = dm1[v]; dm1[v] = d0[v]; d0[v] = dp1[v];
+        }
+        wr.put(i, res);
+    };
+    for (int i0 = 0; i0 < M; i0 += PD) {
+#pragma unroll
+        for (int q = 0; q < PD; ++q) {
+            if (i0 + q >= M) break;
+            step(i0 + q, q);
+        }
+    }
+    if (!periodic) {
+        // phi_old now holds Phi_{M-N-1/2}; rows past the window are added below
+#pragma unroll
+        for (int v = 0; v < V; ++v) acc += phi_old[v];
+        int row0 = r > M - N ? r : M - N;
+        row0 = row0 > 0 ? row0 : 0;
+        for (int row = row0; row < M; ++row) {
+            float x[V];
+            rd.seek(row);
+            rd.next(x);
+#pragma unroll
+            for (int v = 0; v < V; ++v) acc += x[v];
+        }
+        *ofl = acc;
+    }
+}
 
 // ---------------------------------------------------------------------------
 // Uniform walker: every lane of the wave moves in the same direction, so the
@@ -456,15 +571,20 @@ struct RowPipe {
 //   out_i = x_{i-N} - (Phi_{i-N+1/2} - Phi_{i-N-1/2})
 // With zero ghosts the content leaving the upper face of the frame,
 // sum_{r >= M-N} x_r + Phi_{M-N-1/2}, is returned in *ofl.
-// MT > 0 fixes the line length at compile time (full unroll, and for
-// periodic lines the first five rows are kept instead of re-read).
+// MT fixes the line length at compile time (full unroll, and for periodic
+// lines the first five rows are kept instead of re-read); MT = 0 takes it at
+// run time (walk_uniform_any).
 // ---------------------------------------------------------------------------
 template <int V, int MT, bool UNI, class Reader, class Writer>
 __device__ __forceinline__ void walk_uniform(Reader& rd, Writer& wr, const int Mrt,
                                              const LineShift& sh, const bool periodic,
                                              float* ofl)
 {
-    const int M = MT > 0 ? MT : Mrt;
+    if constexpr (MT == 0) {
+        walk_uniform_any<V, UNI>(rd, wr, Mrt, sh, periodic, ofl);
+        return;
+    }
+    constexpr int M = MT;
     const int N = sh.N;
     float xm2[V], xm1[V], x0[V], xp1[V], xp2[V], phi_old[V];
     float dm2[V], dm1[V], d0[V], dp1[V];    // x_{j-1}-x_{j-2}, ..., x_{j+2}-x_{j+1}
@@ -481,9 +601,9 @@ __device__ __forceinline__ void walk_uniform(Reader& rd, Writer& wr, const int M
     rd.seek(r);
     rd.next(xm2); rd.next(xm1); rd.next(x0); rd.next(xp1); rd.next(xp2);
     // rows the loop reads (a periodic line's last five come from head[])
-    const int L = (MT > 0 && periodic) ? M - 5 : M;
+    const int L = periodic ? M - 5 : M;
     RowPipe<V, RowPipeDepth<V, MT>::value, Reader> pipe(rd);
-    if (RowPipeDepth<V, MT>::value > 1) pipe.prime(L);
+    pipe.prime(L);
     if (!periodic) {
         // rows already in the window that lie past the upper face
         auto past = [&](int row) { return row >= M - N && row < M; };
@@ -496,7 +616,7 @@ __device__ __forceinline__ void walk_uniform(Reader& rd, Writer& wr, const int M
             acc += past(r + 4) ? xp2[v] : 0.0f;
         }
     }
-    if (MT > 0 && periodic) {
+    if (periodic) {
 #pragma unroll
         for (int v = 0; v < V; ++v) {
             head[0][v] = xm2[v]; head[1][v] = xm1[v]; head[2][v] = x0[v];
@@ -528,11 +648,11 @@ __device__ __forceinline__ void walk_uniform(Reader& rd, Writer& wr, const int M
 #pragma unroll UNR
     for (int i = 0; i < M; ++i) {
         // new row j+2 for j = i - N
-        if (MT > 0 && periodic && i >= M - 5) {
+        if (periodic && i >= M - 5) {
 #pragma unroll
             for (int v = 0; v < V; ++v) xp2[v] = head[i - (M - 5)][v];
         } else {
-            pipe.take(i, L, xp2);
+            pipe.take(i, i % RowPipeDepth<V, MT>::value, L, xp2);
         }
         if (!periodic) {
             if (r >= M - N && r < M) {
@@ -656,6 +776,77 @@ __device__ __forceinline__ Stencil mixed_stencil(bool neg, float xm2, float xm1,
 }
 
 // ---------------------------------------------------------------------------
+// walk_mixed (below) for a line length known at run time only.
+// ---------------------------------------------------------------------------
+template <int V, class Reader, class Writer>
+__device__ __forceinline__ void walk_mixed_any(Reader& rd, Writer& wr, const int M, const int Nsgn,
+                                           const LineShift& sh)
+{
+    const bool neg = sh.neg;
+    const int Ns = Nsgn;                  // out_i = x_{i-Ns} - (Phi_{i-Ns+1/2} - Phi_{i-Ns-1/2})
+    float xm2[V], xm1[V], x0[V], xp1[V], xp2[V], xp3[V], phi_old[V];
+    float q0[V], q1[V], q2[V], q3[V], q4[V];   // x_{j-1}-x_{j-2}, ..., x_{j+3}-x_{j+2}
+    // carried for flux_mag_mm: curvatures at j+1, j+2 and K_i = d^M4 at
+    // i-1/2 (the minmod of the curvatures at i-1 and i) for i = j .. j+2.
+    // The stencil of a lane moving up has d^M4 = K_j below and K_{j+1}
+    // above; a mirrored lane's (upwind cell j+1) has K_{j+2} and K_{j+1}.
+    float c1[V], c2[V], k0[V], k1[V], k2[V];
+    rd.seek(-Ns - 3);
+    rd.next(xm2); rd.next(xm1); rd.next(x0); rd.next(xp1); rd.next(xp2); rd.next(xp3);
+    constexpr int PD = RowPipeDepth<V, 0>::value;
+    RowPipe<V, PD, Reader> pipe(rd);
+    pipe.prime(M);
+    // flux through (j0-1)+1/2, then slide
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+        q0[v] = xm1[v] - xm2[v];
+        q1[v] = x0[v] - xm1[v];
+        q2[v] = xp1[v] - x0[v];
+        q3[v] = xp2[v] - xp1[v];
+        q4[v] = xp3[v] - xp2[v];
+        const float cm1 = q1[v] - q0[v], c0 = q2[v] - q1[v];
+        c1[v] = q3[v] - q2[v];
+        c2[v] = q4[v] - q3[v];
+        k0[v] = curv_minmod(cm1, c0);
+        k1[v] = curv_minmod(c0, c1[v]);
+        k2[v] = curv_minmod(c1[v], c2[v]);
+        phi_old[v] = flux_mag_mm(mixed_stencil(neg, xm2[v], xm1[v], x0[v], xp1[v], xp2[v], xp3[v],
+                                               q0[v], q1[v], q2[v], q3[v], q4[v]),
+                                 sh, neg ? k2[v] : k0[v], k1[v]);
+        xm2[v] = xm1[v]; xm1[v] = x0[v]; x0[v] = xp1[v]; xp1[v] = xp2[v]; xp2[v] = xp3[v];
+        q0[v] = q1[v]; q1[v] = q2[v]; q2[v] = q3[v]; q3[v] = q4[v];
+    }
+    const float sgn = neg ? -1.0f : 1.0f;
+    auto step = [&](int i, int slot) __attribute__((always_inline)) {
+        pipe.take(i, slot, M, xp3);
+        float res[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            q4[v] = xp3[v] - xp2[v];
+            const float c3 = q4[v] - q3[v];
+            const float k3 = curv_minmod(c2[v], c3);
+            k0[v] = k1[v]; k1[v] = k2[v]; k2[v] = k3;
+            c1[v] = c2[v]; c2[v] = c3;
+            const float phi = flux_mag_mm(mixed_stencil(neg, xm2[v], xm1[v], x0[v], xp1[v], xp2[v],
+                                                        xp3[v], q0[v], q1[v], q2[v], q3[v], q4[v]),
+                                          sh, neg ? k2[v] : k0[v], k1[v]);
+            res[v] = fmaf(-sgn, phi - phi_old[v], x0[v]);
+            phi_old[v] = phi;
+            xm2[v] = xm1[v]; xm1[v] = x0[v]; x0[v] = xp1[v]; xp1[v] = xp2[v]; xp2[v] = xp3[v];
+            q0[v] = q1[v]; q1[v] = q2[v]; q2[v] = q3[v]; q3[v] = q4[v];
+        }
+        wr.put(i, res);
+    };
+    for (int i0 = 0; i0 < M; i0 += PD) {
+#pragma unroll
+        for (int q = 0; q < PD; ++q) {
+            if (i0 + q >= M) break;
+            step(i0 + q, q);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
 // Mixed walker: lanes of one wave may move in opposite directions (the z
 // sweep, where the shift follows the contiguous u_z index).  All lanes walk
 // forward with a 6-cell window; each lane picks its upwind stencil by select.
@@ -665,7 +856,11 @@ template <int V, int MT, class Reader, class Writer>
 __device__ __forceinline__ void walk_mixed(Reader& rd, Writer& wr, const int Mrt, const int Nsgn,
                                            const LineShift& sh)
 {
-    const int M = MT > 0 ? MT : Mrt;
+    if constexpr (MT == 0) {
+        walk_mixed_any<V>(rd, wr, Mrt, Nsgn, sh);
+        return;
+    }
+    constexpr int M = MT;
     const bool neg = sh.neg;
     const int Ns = Nsgn;                  // out_i = x_{i-Ns} - (Phi_{i-Ns+1/2} - Phi_{i-Ns-1/2})
     float xm2[V], xm1[V], x0[V], xp1[V], xp2[V], xp3[V], phi_old[V];
@@ -678,10 +873,10 @@ __device__ __forceinline__ void walk_mixed(Reader& rd, Writer& wr, const int Mrt
     float head[6][V];
     rd.seek(-Ns - 3);
     rd.next(xm2); rd.next(xm1); rd.next(x0); rd.next(xp1); rd.next(xp2); rd.next(xp3);
-    const int L = MT > 0 ? M - 6 : M;           // rows the loop reads
+    const int L = M - 6;           // rows the loop reads
     RowPipe<V, RowPipeDepth<V, MT>::value, Reader> pipe(rd);
-    if (RowPipeDepth<V, MT>::value > 1) pipe.prime(L);
-    if (MT > 0) {
+    pipe.prime(L);
+    {
 #pragma unroll
         for (int v = 0; v < V; ++v) {
             head[0][v] = xm2[v]; head[1][v] = xm1[v]; head[2][v] = x0[v];
@@ -712,11 +907,11 @@ __device__ __forceinline__ void walk_mixed(Reader& rd, Writer& wr, const int Mrt
     constexpr int UNR = MT > 0 ? MT : 1;
 #pragma unroll UNR
     for (int i = 0; i < M; ++i) {
-        if (MT > 0 && i >= M - 6) {
+        if (i >= M - 6) {
 #pragma unroll
             for (int v = 0; v < V; ++v) xp3[v] = head[i - (M - 6)][v];
         } else {
-            pipe.take(i, L, xp3);
+            pipe.take(i, i % RowPipeDepth<V, MT>::value, L, xp3);
         }
         float res[V];
 #pragma unroll
@@ -823,7 +1018,7 @@ __device__ __forceinline__ void walk_pair(Reader& rd, Writer& wr, const LineShif
             x[0] = head[i - L][0];
             x[1] = head[i - L][1];
         } else {
-            pipe.take(i, L, x);
+            pipe.take(i, i % PD, L, x);
         }
         a[4] = carry;                              // row i + 2
         carry = x[0];
