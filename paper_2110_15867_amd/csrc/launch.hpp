@@ -100,6 +100,20 @@ bool kick_any_supported(int prec, const int nu[3], size_t lds_limit);
 hipError_t launch_kick_any(int prec, const void* fin, const float* sin, void* fout, float* sout,
                            const KickArgs& a, hipStream_t st);
 
+// y and x drifts in one pass (FP32 storage; drift.hip)
+struct DriftAxis {
+    int n, nu;                  // cells along the axis, velocity cells along its velocity axis
+    double umax, du, factor;    // s_j = (-umax + (j + 1/2) du) factor, factor = dt a^-2 / dx
+};
+struct DriftArgs {
+    DriftAxis x, y;
+    int nz, nuz;
+    long Nu;
+    int W, zi, jchunks;         // lanes of a wave (set by the launcher): W u_z values of zi z cells
+};
+bool drift_yx_supported(const DriftArgs& a);
+hipError_t launch_drift_yx(const float* fin, float* fout, DriftArgs a, hipStream_t st);
+
 struct MomArgs {
     long cells;
     long Nu;
