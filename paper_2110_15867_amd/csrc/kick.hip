@@ -19,11 +19,25 @@
 // finished block's stores drain behind the next block's arithmetic: the LDS
 // holds one block, so this is the only way its HBM traffic overlaps compute.
 //
-// LDS layout: uz-lines of NU values padded to NU+1 floats, line index
-// jx*NU + jy.  A thread owns one line per sweep; lanes of a wave read
-// consecutive jz (ux, uy sweeps) or lines NU+1 floats apart (uz sweep), both
-// free of bank conflicts.  Lines of one sweep are disjoint, so a thread may
-// overwrite its own line as soon as it has read it.
+// LDS layout: uz-lines of NU values, line index jx*NU + jy, padded so that
+// every access is free of bank conflicts.  FP32: to NU+4 floats -- lanes over
+// jz touch consecutive banks, and the 16-byte groups of eight consecutive
+// lines (or of one line) fill the 32 banks once, so the uz sweep and the
+// store move 16 bytes per lane and instruction.  FP16/BF16: to NU+1 floats,
+// one value at a time (with 16-byte accesses the FP16 kick took 1.5 % longer).
+// A thread owns one line per sweep; lines of one sweep are disjoint, so a
+// thread may overwrite its own line as soon as it has read it.
+//
+// With FP32 storage a thread's first line, along ux, comes straight from HBM:
+// its values lie one uy-uz plane apart, and the lanes of a wave read
+// consecutive addresses of each plane.  So the next block's lines, requested
+// after the ux sweep of the one before, wait in registers and need no pass
+// through LDS.  Measured on 64 x 64 x 32 cells of 32^3: 10.2 -> 9.2 ms per
+// kick for this and the 16-byte accesses (32^3 cells: 2.70 -> 2.62).
+// Tried and slower: evaluating the curvature minmods only where a wave fails
+// the Suresh-Huynh test (flux_mag_lazy: 9.7 ms, 64^3 blocks 2.25 -> 2.55);
+// one walk for the three axes and both directions, a quarter of the code,
+// with a line's results stored after its walk (10.3 ms).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -32,6 +46,14 @@
 #include "sl_mpp5.hpp"
 
 namespace vlasov {
+
+// The block in LDS: uz-lines of NU values, LS floats apart.
+template <int P, int NU>
+struct KickLds {
+    static constexpr int LS = Codec<P>::scaled ? NU + 1 : NU + 4;
+    // first value of the four-value group of block element e (a multiple of 4)
+    __device__ static int group(int e) { return (e / NU) * LS + e % NU; }
+};
 
 // One thread's share of a velocity block in flight from HBM: NS slots of 4
 // consecutive values of one uz-line, with that line's scale.
@@ -66,16 +88,14 @@ struct BlockSlots {
             sc[s] = Codec<P>::scaled ? ssrc[e / NU] : 1.0f;
         }
     }
-    // decoded values into the padded LDS block
+    // decoded values into the LDS block
     __device__ void put(float* lds, int t) const
     {
 #pragma unroll
         for (int s = 0; s < NS; ++s) {
-            const int e = elem(s, t);
-            float* dst = lds + (e / NU) * (NU + 1) + e % NU;
+            float* dst = lds + KickLds<P, NU>::group(elem(s, t));
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
-                dst[u] = decode<P>(q[s].v[u], sc[s]);
+            for (int u = 0; u < 4; ++u) dst[u] = decode<P>(q[s].v[u], sc[s]);
         }
     }
 };
@@ -101,10 +121,10 @@ __device__ __forceinline__ void read_line(const float* line, float (&x)[M])
 // periodic lines rotate.  (Rare in practice -- a kick moves less than one
 // cell per half step unless the field is strong -- so the addressing here is
 // plain runtime arithmetic.)
-template <int M, int S, bool NEG, bool PER>
-__device__ __forceinline__ float translate_line(float* line, int N, float phi_top)
+// at(p): frame position p of the line.
+template <int M, bool PER, class At>
+__device__ __forceinline__ float translate_line(At&& at, int N, float phi_top)
 {
-    auto at = [&](int p) -> float& { return line[(NEG ? M - 1 - p : p) * S]; };
     if (PER && M <= 32) {
         float z[M];
 #pragma unroll
@@ -167,7 +187,7 @@ __device__ __forceinline__ float kick_axis_dir(float* line, const LineShift& sh,
     });
     float ofl = PER ? 0.0f : phi_top;            // N = 0: Phi_{M-1/2} leaves
     if (N > 0) {
-        ofl = translate_line<M, S, NEG, PER>(line, N, phi_top);
+        ofl = translate_line<M, PER>(at, N, phi_top);
         if (SCALE && !PER) {
             m = 0.0f;                            // only what stayed
             for (int p = N; p < M; ++p) m = fmaxf(m, fabsf(at(p)));
@@ -181,19 +201,15 @@ __device__ __forceinline__ float kick_axis_dir(float* line, const LineShift& sh,
     return ofl;
 }
 
-template <int P, int NU, bool PER, int AXIS>
-__device__ __forceinline__ float kick_axis(float* lds, float* sout_line, float* lmax_line,
-                                           const KickArgs& a, const KickShift* __restrict__ tab,
-                                           int cell, float g, int t)
+// The split of the shift of (cell, axis): scalar loads of the precomputed one
+// (uniform over the work-group), or made here.
+template <int NU, bool PER>
+__device__ __forceinline__ LineShift kick_shift(const KickArgs& a, const KickShift* __restrict__ tab,
+                                                int cell, int axis, float g)
 {
-    constexpr int LS = NU + 1;
-    const int base = AXIS == 0 ? (t / NU) * LS + (t % NU)
-                   : AXIS == 1 ? (t / NU) * NU * LS + (t % NU)
-                               : t * LS;
     LineShift sh;
     if (tab != nullptr) {
-        // scalar loads of the precomputed split (uniform over the work-group)
-        const KickShift e = tab[(long)cell * 3 + AXIS];
+        const KickShift e = tab[(long)cell * 3 + axis];
         sh.N = e.N;
         sh.neg = (e.flags & 1) != 0;
         sh.comp = (e.flags & 2) != 0;
@@ -201,12 +217,93 @@ __device__ __forceinline__ float kick_axis(float* lds, float* sout_line, float* 
         sh.v0 = e.v0; sh.v1 = e.v1; sh.v2 = e.v2; sh.v3 = e.v3;
         sh.alpha = e.alpha; sh.q = e.q; sh.alpha_c = e.alpha_c; sh.muc = e.muc;
     } else {
-        sh = split_shift((double)g * a.factor[AXIS], NU, PER);
+        sh = split_shift((double)g * a.factor[axis], NU, PER);
     }
-    const int N = uniform_sgpr(sh.N);
-    if (uniform_sgpr(sh.neg ? 1 : 0))
-        return kick_axis_dir<P, NU, PER, AXIS, true>(lds + base, sh, N, sout_line, lmax_line);
-    return kick_axis_dir<P, NU, PER, AXIS, false>(lds + base, sh, N, sout_line, lmax_line);
+    return sh;
+}
+
+// ux sweep of thread t's line (jy, jz) = (t / NU, t % NU), its values in x in
+// u_x order: the result goes to LDS.
+template <int NU, bool PER, bool NEG>
+__device__ __forceinline__ float kick_ux_regs(float* lds, const float (&x)[NU], const LineShift& sh,
+                                              int N, int t)
+{
+    constexpr int M = NU;
+    constexpr int LS = KickLds<PREC_F32, NU>::LS;
+    float* line = lds + (t / NU) * LS + t % NU;
+    auto at = [&](int p) -> float& { return line[(NEG ? M - 1 - p : p) * (NU * LS)]; };
+    float f[M];
+#pragma unroll
+    for (int k = 0; k < M; ++k) f[k] = x[NEG ? M - 1 - k : k];
+    const float phi_top = line_update_regs<M, PER>(f, sh, [&](int j, float v) { at(j) = v; });
+    if (N > 0) return translate_line<M, PER>(at, N, phi_top);
+    return PER ? 0.0f : phi_top;
+}
+
+// uy sweep of thread t's line (jx, jz) = (t / NU, t % NU).
+template <int NU, bool PER, bool NEG>
+__device__ __forceinline__ float kick_uy(float* lds, const LineShift& sh, int N, int t)
+{
+    constexpr int M = NU, LS = KickLds<PREC_F32, NU>::LS;
+    float* line = lds + (t / NU) * (NU * LS) + t % NU;
+    auto at = [&](int p) -> float& { return line[(NEG ? M - 1 - p : p) * LS]; };
+    float x[M];
+#pragma unroll
+    for (int k = 0; k < M; ++k) x[k] = at(k);
+    const float phi_top = line_update_regs<M, PER>(x, sh, [&](int j, float v) { at(j) = v; });
+    if (N > 0) return translate_line<M, PER>(at, N, phi_top);
+    return PER ? 0.0f : phi_top;
+}
+
+// uz sweep of thread t's line t, sixteen bytes at a time.
+template <int NU, bool PER, bool NEG>
+__device__ __forceinline__ float kick_uz(float* lds, const LineShift& sh, int N, int t)
+{
+    constexpr int M = NU;
+    float* line = lds + t * KickLds<PREC_F32, NU>::LS;
+    float x[M], y[M];
+#pragma unroll
+    for (int g = 0; g < M; g += 4) {
+        const float4 q = *reinterpret_cast<const float4*>(line + g);
+        const float v[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) x[NEG ? M - 1 - (g + u) : g + u] = v[u];
+    }
+    const float phi_top = line_update_regs<M, PER>(x, sh, [&](int j, float v) {
+        y[j] = v;
+        // a group is written when its last value is known (for PER, y_0 comes
+        // last of all)
+        const int j0 = j & ~3;
+        if (PER && j0 == 0 ? j == 0 : (j & 3) == 3) {
+            const int g = NEG ? M - 4 - j0 : j0;
+            *reinterpret_cast<float4*>(line + g) =
+                NEG ? make_float4(y[j0 + 3], y[j0 + 2], y[j0 + 1], y[j0])
+                    : make_float4(y[j0], y[j0 + 1], y[j0 + 2], y[j0 + 3]);
+        }
+    });
+    if (N > 0)
+        return translate_line<M, PER>(
+            [&](int p) -> float& { return line[NEG ? M - 1 - p : p]; }, N, phi_top);
+    return PER ? 0.0f : phi_top;
+}
+
+// Sweep along AXIS of thread t's line out of LDS (scaled storage; FP32: uy and
+// uz).
+template <int P, int NU, bool PER, int AXIS, bool NEG>
+__device__ __forceinline__ float kick_sweep(float* lds, const LineShift& sh, int N, int t,
+                                            float* sout, float* lmax)
+{
+    if constexpr (Codec<P>::scaled) {
+        constexpr int LS = KickLds<P, NU>::LS;
+        float* line = lds + (AXIS == 0   ? (t / NU) * LS + t % NU
+                             : AXIS == 1 ? (t / NU) * (NU * LS) + t % NU
+                                         : t * LS);
+        return kick_axis_dir<P, NU, PER, AXIS, NEG>(line, sh, N, sout + t, lmax + t);
+    } else if constexpr (AXIS == 1) {
+        return kick_uy<NU, PER, NEG>(lds, sh, N, t);
+    } else {
+        return kick_uz<NU, PER, NEG>(lds, sh, N, t);
+    }
 }
 
 // Outflow of one block, first half: the FP64 sums of the three per-thread
@@ -297,15 +394,34 @@ __global__ void __launch_bounds__(NU * NU) k_kick(const typename Codec<P>::T* __
     int cell = blockIdx.x;
     if (cell >= ncell) return;                  // uniform over the work-group
 
+    // FP32: the lines along ux in registers (see above); else the block's slots
+    constexpr bool DIRECT = !Codec<P>::scaled;
     Slots R;
-    R.load(fin, sin, a, cell, fresh_tid());
-    R.put(lds, fresh_tid());
-    float g[3];                                 // field of the cell in LDS (scalar)
+    float xr[DIRECT ? NU : 1];
+    float g[3], gn[3];      // field of the cell in hand, and (DIRECT) of the next
+    auto request = [&](int c) {
+        if constexpr (DIRECT) {
 #pragma unroll
-    for (int k = 0; k < 3; ++k) g[k] = uniform_f32(R.g[k]);
+            for (int k = 0; k < 3; ++k) gn[k] = a.g[(long)k * a.cells + c];
+            const T* src = fin + (long)c * NV + fresh_tid();
+#pragma unroll
+            for (int k = 0; k < NU; ++k) xr[k] = Codec<P>::dec(src[k * NT]);
+        } else {
+            R.load(fin, sin, a, c, fresh_tid());
+        }
+    };
+    auto arrive = [&]() {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) g[k] = uniform_f32(DIRECT ? gn[k] : R.g[k]);
+        if constexpr (!DIRECT) R.put(lds, fresh_tid());
+    };
+    request(cell);
+    arrive();
     int next = uniform_sgpr(cell + (int)gridDim.x);
-    if (next < ncell) R.load(fin, sin, a, next, fresh_tid());
-    __syncthreads();
+    if constexpr (!DIRECT) {
+        if (next < ncell) request(next);
+        __syncthreads();
+    }
 
     const bool ofl = a.outflow != nullptr && !PER;
     const bool mom = a.rho != nullptr;
@@ -318,12 +434,36 @@ __global__ void __launch_bounds__(NU * NU) k_kick(const typename Codec<P>::T* __
         double prev = 0.0;
         if (ofl && t == 0) prev = a.outflow[cell];
         float o[3];
-        o[0] = kick_axis<P, NU, PER, 0>(lds, nullptr, nullptr, a, tab, cell, g[0], t);
+        {
+            const LineShift sh = kick_shift<NU, PER>(a, tab, cell, 0, g[0]);
+            const int N = uniform_sgpr(sh.N);
+            const bool neg = uniform_sgpr(sh.neg ? 1 : 0) != 0;
+            if constexpr (DIRECT) {
+                o[0] = neg ? kick_ux_regs<NU, PER, true>(lds, xr, sh, N, fresh_tid())
+                           : kick_ux_regs<NU, PER, false>(lds, xr, sh, N, fresh_tid());
+                if (next < ncell) request(next);
+            } else {
+                o[0] = neg ? kick_sweep<P, NU, PER, 0, true>(lds, sh, N, fresh_tid(), nullptr, nullptr)
+                           : kick_sweep<P, NU, PER, 0, false>(lds, sh, N, fresh_tid(), nullptr, nullptr);
+            }
+        }
         __syncthreads();
-        o[1] = kick_axis<P, NU, PER, 1>(lds, nullptr, nullptr, a, tab, cell, g[1], t);
+        {
+            const LineShift sh = kick_shift<NU, PER>(a, tab, cell, 1, g[1]);
+            const int N = uniform_sgpr(sh.N);
+            o[1] = uniform_sgpr(sh.neg ? 1 : 0)
+                       ? kick_sweep<P, NU, PER, 1, true>(lds, sh, N, fresh_tid(), nullptr, nullptr)
+                       : kick_sweep<P, NU, PER, 1, false>(lds, sh, N, fresh_tid(), nullptr, nullptr);
+        }
         __syncthreads();
-        o[2] = kick_axis<P, NU, PER, 2>(lds, Codec<P>::scaled ? sout + (long)cell * NL + t : nullptr,
-                                        lmax + t, a, tab, cell, g[2], t);
+        {
+            const LineShift sh = kick_shift<NU, PER>(a, tab, cell, 2, g[2]);
+            const int N = uniform_sgpr(sh.N);
+            float* sl = Codec<P>::scaled ? sout + (long)cell * NL : nullptr;
+            o[2] = uniform_sgpr(sh.neg ? 1 : 0)
+                       ? kick_sweep<P, NU, PER, 2, true>(lds, sh, N, fresh_tid(), sl, lmax)
+                       : kick_sweep<P, NU, PER, 2, false>(lds, sh, N, fresh_tid(), sl, lmax);
+        }
         if (ofl) wave_sums3<NT>(o, red);
         __syncthreads();
         if (ofl && t < 64) outflow_total<NT>(red, prev, a.du3, a.outflow + cell);
@@ -338,7 +478,15 @@ __global__ void __launch_bounds__(NU * NU) k_kick(const typename Codec<P>::T* __
 #pragma unroll
         for (int s = 0; s < Slots::NS; ++s) {
             const int e = Slots::elem(s, ts);
-            float* src = lds + (e / NU) * (NU + 1) + e % NU;
+            const float* at = lds + KickLds<P, NU>::group(e);
+            float src[4];
+            if constexpr (DIRECT) {
+                const float4 v = *reinterpret_cast<const float4*>(at);
+                src[0] = v.x; src[1] = v.y; src[2] = v.z; src[3] = v.w;
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) src[u] = at[u];
+            }
             const float inv = Codec<P>::scaled ? inv_scale(lmax[e / NU]) : 1.0f;
             Pack<T, 4> q;
 #pragma unroll
@@ -374,12 +522,10 @@ __global__ void __launch_bounds__(NU * NU) k_kick(const typename Codec<P>::T* __
             mcell = cell;
         }
         if (next >= ncell) break;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) g[k] = uniform_f32(R.g[k]);
-        R.put(lds, ts);
+        arrive();
         cell = next;
         next = uniform_sgpr(cell + (int)gridDim.x);
-        if (next < ncell) R.load(fin, sin, a, next, fresh_tid());
+        if (!DIRECT && next < ncell) request(next);
         __syncthreads();
     }
     if (mom) {
@@ -760,7 +906,7 @@ static hipError_t launch_kick_t(const void* fin, const float* sin, void* fout, f
                                 const KickArgs& a, const KickShift* tab, hipStream_t st)
 {
     using T = typename Codec<P>::T;
-    const size_t lds = (size_t)N * N * (N + 1) * sizeof(float);
+    const size_t lds = (size_t)N * N * KickLds<P, N>::LS * sizeof(float);
     auto kern = k_kick<P, N, PER>;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -796,8 +942,8 @@ bool kick_supported(const int nu[3], size_t lds_limit)
 {
     if (nu[0] != nu[1] || nu[1] != nu[2]) return false;
     if (nu[0] != 16 && nu[0] != 32) return false;
-    const size_t lds = (size_t)nu[0] * nu[0] * (nu[0] + 1) * sizeof(float);
-    return lds <= lds_limit;
+    const size_t lds = (size_t)nu[0] * nu[0] * (nu[0] + 4) * sizeof(float);
+    return lds + 6144 <= lds_limit;           // (and the static part)
 }
 
 hipError_t launch_kick(int prec, const void* fin, const float* sin, void* fout, float* sout,
