@@ -108,8 +108,9 @@ void split_integer(double s, int M, int* N, bool* neg)
 // Whether the z sweep can pair the two halves of each uz-line in one lane
 // (see k_position_pair): every line of the upper half must move up and every
 // line of the lower half down, all by less than one cell; the half length
-// must divide the wave, a row must hold whole waves of lanes and the line
-// length must have a compiled walk.  Returns 1 when it can, else 0.
+// must divide the wave, a row must hold whole waves of lanes and the line must
+// have 64 cells (shorter ones go through LDS tiles).  Returns 1 when it can,
+// else 0.
 int pair_mode(const PosArgs& a)
 {
     const long nuz = a.nuz;
@@ -117,7 +118,7 @@ int pair_mode(const PosArgs& a)
     if (a.V != 1 || a.pst != 1 || a.nshift != nuz || nuz % 2 != 0) return 0;
     if (H != 8 && H != 16 && H != 32) return 0;
     if ((a.I / 2) % 64 != 0) return 0;
-    if (a.M != 16 && a.M != 32 && a.M != 64) return 0;
+    if (a.M != 64) return 0;
     for (long j = 0; j < nuz; ++j) {
         int n;
         bool neg;
@@ -202,7 +203,7 @@ int run_position(const vlasov_grid* g, const Dims& d, int axis, int prec, const 
 
 // Arguments of the fused y and x drifts, where they can run fused: FP32 storage
 // and a shape the kernel takes.  The single drifts are bound by HBM: one pass
-// over f instead of two (64 x 64 x 32 cells of 32^3: 13.8 -> 8.9 ms).
+// over f instead of two (64 x 64 x 32 cells of 32^3: 13.8 -> 8.8 ms).
 // FP16/BF16 drifts are bound by their vector arithmetic, which fusing does
 // not reduce.
 bool fuse_drifts(const vlasov_grid* g, const Dims& d, int prec, double dta, DriftArgs& a)

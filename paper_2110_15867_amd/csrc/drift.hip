@@ -18,9 +18,10 @@
 // (S + 1) / S, and the x-windows take 6 S registers of the 128 that four waves
 // per SIMD leave (carrying the planes' differences too would save three
 // instructions per cell but spills at S = 8: twice the time).
-// Measured on 64 x 64 x 32 cells of 32^3: 8.9 ms against 13.8 for the two
-// drifts, 3.9 TB/s and 70 vector instructions per cell, 0.85 of the vector
-// issue rate; 32^3 of 32^3 with shifts of 2.5 cells 2.27 ms against 3.28.
+// Measured on 64 x 64 x 32 cells of 32^3: 8.8 ms against 13.8 for the two
+// drifts, 3.9 TB/s and 0.85 of the vector issue rate; 32^3 of 32^3 with shifts
+// of 2.5 cells 2.19 ms against 3.28.  (The curvature minmods evaluated only
+// where a wave fails the Suresh-Huynh test: 8.9 and 2.27 ms.)
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -97,12 +98,11 @@ __global__ void __launch_bounds__(1024) k_drift_yx(const float* __restrict__ fin
     float nxt[S + 5];
     load_plane(nxt);
     float w[5][S], phi_old[S];
-    LazyMinmod kx[S];
+    float kx[S];              // curvature minmod below the next interface
 #pragma unroll
     for (int s = 0; s < S; ++s) {
         phi_old[s] = 0.0f;
-        kx[s].have = 0;
-        kx[s].m = 0.0f;
+        kx[s] = 0.0f;
 #pragma unroll
         for (int q = 0; q < 5; ++q) w[q][s] = 0.0f;
     }
@@ -119,19 +119,20 @@ __global__ void __launch_bounds__(1024) k_drift_yx(const float* __restrict__ fin
 #pragma unroll
                 for (int k = 0; k < S + 5; ++k) v[k] = nxt[k];
                 if (t + 1 < nx) load_plane(nxt);
-                LazyMinmod ky;
-                ky.have = 0;
-                ky.m = 0.0f;
                 float dm2 = v[1] - v[0], dm1 = v[2] - v[1], d0 = v[3] - v[2], dp1 = v[4] - v[3];
-                float phi = flux_mag_lazy(Stencil{v[0], v[1], v[2], v[3], v[4], dm2, dm1, d0, dp1},
-                                          sy, ky);
+                float cy = dp1 - d0, ky = curv_minmod(d0 - dm1, cy);
+                float phi = flux_mag_mm(Stencil{v[0], v[1], v[2], v[3], v[4], dm2, dm1, d0, dp1}, sy,
+                                        curv_minmod(dm1 - dm2, d0 - dm1), ky);
 #pragma unroll
                 for (int s = 0; s < S; ++s) {
                     dm2 = dm1; dm1 = d0; d0 = dp1;
                     dp1 = v[s + 5] - v[s + 4];
-                    const float ph = flux_mag_lazy(
+                    const float cn = dp1 - d0, kn = curv_minmod(cy, cn);
+                    const float ph = flux_mag_mm(
                         Stencil{v[s + 1], v[s + 2], v[s + 3], v[s + 4], v[s + 5], dm2, dm1, d0, dp1},
-                        sy, ky);
+                        sy, ky, kn);
+                    cy = cn;
+                    ky = kn;
                     w[q][s] = v[s + 3] - (ph - phi);
                     phi = ph;
                 }
@@ -152,8 +153,11 @@ __global__ void __launch_bounds__(1024) k_drift_yx(const float* __restrict__ fin
             for (int s = 0; s < S; ++s) {
                 const float xa = w[(q + 1) % 5][s], xb = w[(q + 2) % 5][s], xc = w[(q + 3) % 5][s];
                 const float xd = w[(q + 4) % 5][s], xe = w[q][s];
-                const float ph = flux_mag_lazy(Stencil{xa, xb, xc, xd, xe, xb - xa, xc - xb, xd - xc, xe - xd},
-                                               sx, kx[s]);
+                const float e0 = xb - xa, e1 = xc - xb, e2 = xd - xc, e3 = xe - xd;
+                const float c0 = e2 - e1, kn = curv_minmod(c0, e3 - e2);
+                const float kb = t == 4 ? curv_minmod(e1 - e0, c0) : kx[s];
+                const float ph = flux_mag_mm(Stencil{xa, xb, xc, xd, xe, e0, e1, e2, e3}, sx, kb, kn);
+                kx[s] = kn;
                 if (t >= 5)
                     __builtin_amdgcn_raw_buffer_store_b32(
                         __builtin_bit_cast(unsigned, xc - (ph - phi_old[s])), ro, (int)voff, (int)rout[s], 0);

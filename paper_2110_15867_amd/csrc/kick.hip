@@ -35,7 +35,8 @@
 // through LDS.  Measured on 64 x 64 x 32 cells of 32^3: 10.2 -> 9.2 ms per
 // kick for this and the 16-byte accesses (32^3 cells: 2.70 -> 2.62).
 // Tried and slower: evaluating the curvature minmods only where a wave fails
-// the Suresh-Huynh test (flux_mag_lazy: 9.7 ms, 64^3 blocks 2.25 -> 2.55);
+// the Suresh-Huynh test, one or two as the interface before it did (9.7 ms;
+// 64^3 blocks 2.25 -> 2.55);
 // one walk for the three axes and both directions, a quarter of the code,
 // with a line's results stored after its walk (10.3 ms).
 #include <hip/hip_runtime.h>

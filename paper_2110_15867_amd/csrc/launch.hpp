@@ -48,6 +48,10 @@ struct VelArgs {
 
 hipError_t launch_position(int prec, const void* fin, const float* sin, void* fout, float* sout,
                            const PosArgs& a, hipStream_t st);
+// z sweep through LDS tiles of whole z-lines (zdrift.hip)
+bool z_tiles_supported(const PosArgs& a);
+hipError_t launch_z_tiles(int prec, const void* fin, const float* sin, void* fout, float* sout,
+                          const PosArgs& a, hipStream_t st);
 hipError_t launch_vel_strided(int prec, const void* fin, const float* sin, void* fout, float* sout,
                               const VelArgs& a, hipStream_t st);
 hipError_t launch_vel_uz(int prec, const void* fin, const float* sin, void* fout, float* sout,

@@ -217,13 +217,25 @@ hipError_t launch_moments_adj(const MomArgs& a, const double* lam_rho, const dou
 }
 
 // One work-group, fixed order: thread t sums x[t], x[t+1024], ..., then a
-// fixed tree over the threads.
+// fixed tree over the threads.  Bound by load latency, so U values are in
+// flight per thread before the first is added (262144 values: one at a time
+// 117 us, 46 us).
 __global__ void __launch_bounds__(1024) k_sum(const double* __restrict__ x, long n, double scale,
                                               double* __restrict__ out)
 {
     __shared__ double red[16];
     double s = 0.0;
-    for (long i = threadIdx.x; i < n; i += blockDim.x) s += x[i];
+    constexpr int U = 16;
+    const long stride = blockDim.x;
+    long i = threadIdx.x;
+    for (; i + (U - 1) * stride < n; i += U * stride) {
+        double v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = x[i + u * stride];
+#pragma unroll
+        for (int u = 0; u < U; ++u) s += v[u];
+    }
+    for (; i < n; i += stride) s += x[i];
     s = wave_sum(s);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) red[wave] = s;

@@ -390,51 +390,6 @@ __device__ __forceinline__ float flux_mag_mm(const Stencil& s, const LineShift& 
     return med3(pre, 0.0f, s.c);
 }
 
-// The curvature minmod carried between the interfaces of a line only where it
-// was needed: m is d^M4 at the lower face of the next interface if `have`
-// (the same for the whole wave).
-struct LazyMinmod {
-    float m;
-    int have;
-};
-
-// flux_mag_mm evaluating the curvature minmods only where some lane of the
-// wave fails the Suresh-Huynh test: one if the interface before it also
-// needed them, else two.  For lines with one shift per wave.  Same bits.
-// A walk that evaluates one per interface (flux_mag_mm) spends five
-// instructions on every interface and fourteen more on a failing one; this
-// spends none and 21, or 26 after an interface that passed: less work below
-// about nine failing waves in ten.
-__device__ __forceinline__ float flux_mag_lazy(const Stencil& s, const LineShift& sh, LazyMinmod& k)
-{
-    float y = sh.v0 * s.dm2;                            // fhat - f_j
-    y = fmaf(sh.v1, s.dm1, y);
-    y = fmaf(sh.v2, s.d0, y);
-    y = fmaf(sh.v3, s.dp1, y);
-    const float m = med3(s.d0, sh.alpha * s.dm1, 0.0f); // f_MP - f_j
-    float pre = sh.mu * (s.c + y);
-    const bool fails = med3(y, 0.0f, m) != y;
-    if (__ballot(fails) != 0) {
-        const float D0 = s.d0 - s.dm1;
-        const float Mp = curv_minmod(D0, s.dp1 - s.d0);
-        if (!k.have) k.m = curv_minmod(s.dm1 - s.dm2, D0);
-        float lim;
-        if (!sh.comp) {
-            lim = sh.mu * mp_bounded_m(s.c + y, s, sh.alpha, k.m, Mp);
-        } else {
-            const Stencil r{s.e, s.d, s.c, s.b, s.a, -s.dp1, -s.d0, -s.dm1, -s.dm2};
-            const float ghat = fmaf(-sh.q, y, s.c);
-            lim = fmaf(-sh.muc, mp_bounded_m(ghat, r, sh.alpha_c, Mp, k.m), s.c);
-        }
-        pre = fails ? lim : pre;
-        k.m = Mp;
-        k.have = 1;
-    } else {
-        k.have = 0;
-    }
-    return med3(pre, 0.0f, s.c);
-}
-
 // The constants of a line whose shift is the same in every lane of the wave,
 // moved to scalar registers.
 __device__ __forceinline__ LineShift uniform_shift(const LineShift& sh)

@@ -399,17 +399,12 @@ inline hipError_t launch_position_v(const void* fin, const float* sin, void* fou
     // its vector ALU work; with FP32 storage it is bound by memory and the
     // per-lane walk, with half the bytes per wave row, measured faster.
     if constexpr (V == 1 && Codec<P>::scaled) if (a.pair != 0) {
-        // the host checked: nu_z in {16, 32, 64}, M in {16, 32, 64}
+        // the host checked: nu_z in {16, 32, 64}, M = 64
         const unsigned pblocks = (unsigned)((a.O * (a.I / 2) + 255) / 256);
-#define VL_PAIR(MTV, HV) \
-    hipLaunchKernelGGL((k_position_pair<P, MTV, HV>), dim3(pblocks), dim3(256), 0, st, (const T*)fin, sin, (T*)fout, sout, a)
-#define VL_PAIR_M(HV) \
-    switch (a.M) { case 16: VL_PAIR(16, HV); break; case 32: VL_PAIR(32, HV); break; default: VL_PAIR(64, HV); break; }
-        if (a.nuz == 16) { VL_PAIR_M(8) }
-        else if (a.nuz == 32) { VL_PAIR_M(16) }
-        else { VL_PAIR_M(32) }
-#undef VL_PAIR_M
-#undef VL_PAIR
+        auto kern = a.nuz == 16   ? k_position_pair<P, 64, 8>
+                    : a.nuz == 32 ? k_position_pair<P, 64, 16>
+                                  : k_position_pair<P, 64, 32>;
+        hipLaunchKernelGGL(kern, dim3(pblocks), dim3(256), 0, st, (const T*)fin, sin, (T*)fout, sout, a);
         return hipGetLastError();
     }
     // uz-lines of 32 values (the usual velocity block) get the compile-time
