@@ -360,8 +360,15 @@ hipError_t launch_any_p(const void* fin, const float* sin, void* fout, float* so
 bool kick_any_supported(int prec, const int nu[3], size_t lds_limit)
 {
     // (2 KiB for the static part; indices inside a block stay below 2^16)
-    return (double)nu[0] * nu[1] * (nu[2] + 2.0) < 60000.0 &&
-           any_lds_bytes(prec, nu) + 2048 <= lds_limit;
+    if ((double)nu[0] * nu[1] * (nu[2] + 2.0) >= 60000.0) return false;
+    const size_t lds = any_lds_bytes(prec, nu) + 2048;
+    if (lds > lds_limit) return false;
+    // FP16/BF16 blocks that leave room for one work-group per CU round their
+    // intermediate values in LDS with nothing to overlap it: taken only where
+    // no strided sweep has a compiled line length (16 x 16 x 12 cells, FP16:
+    // 40 x 16 x 32 0.35 ms, 0.31 as three sweeps; 33 x 36 x 32 0.63 and 0.72)
+    auto compiled = [](int m) { return m == 16 || m == 32 || m == 64; };
+    return prec == PREC_F32 || 2 * lds <= lds_limit || !(compiled(nu[0]) || compiled(nu[1]));
 }
 
 hipError_t launch_kick_any(int prec, const void* fin, const float* sin, void* fout, float* sout,

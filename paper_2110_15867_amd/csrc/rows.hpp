@@ -21,6 +21,7 @@ namespace vlasov {
 template <int P, int V, bool SCALED = Codec<P>::scaled>
 struct GlobalReader {
     using T = typename Codec<P>::T;
+    static constexpr bool decodes = Codec<P>::scaled;
     const T* base;        // element (o, row 0, k)
     const float* sbase;   // scale of (o, row 0, k) (scaled storage)
     long stride;          // elements between rows
@@ -197,6 +198,7 @@ __device__ __forceinline__ void buffer_store_pack(const Pack<T, V>& q, __amdgpu_
 template <int P, int V>
 struct URowReader {
     using T = typename Codec<P>::T;
+    static constexpr bool decodes = Codec<P>::scaled;
     const T* base;        // row 0 of the wave's first element (uniform)
     const float* sbase;   // its scale (uniform; scaled storage)
     unsigned loff;        // this lane's byte offset within a row
@@ -385,6 +387,7 @@ struct PairRowWriter {
 // Rows of one line held in LDS (already decoded to FP32), `stride` floats
 // apart.
 struct LdsReader {
+    static constexpr bool decodes = false;
     const float* line;
     int stride;
     int M;

@@ -418,13 +418,15 @@ __device__ __forceinline__ LineShift uniform_shift(const LineShift& sh)
 // compile time a walk is fully unrolled; otherwise it is unrolled by the ring
 // (one row at a time, the walk of a short line is a chain of load latencies:
 // z of 20 x 18 x 15 cells of 24 x 20 x 18 took 132 us, 110 with four rows in
-// flight).  The walks read rows strictly in order; take(i) hands out the i-th
-// row of the walk's loop and requests row i + PD, never beyond the L rows the
-// loop consumes.
+// flight; readers that decode FP16/BF16 codes, which the walk's arithmetic
+// bounds, keep one: with four, x and y of 8^3 cells of 64^3 took 10 % longer).
+// The walks read rows strictly in order; take(i) hands out the i-th row of
+// the walk's loop and requests row i + PD, never beyond the L rows the loop
+// consumes.
 // ---------------------------------------------------------------------------
-template <int V, int MT>
+template <int V, int MT, bool DEC = false>
 struct RowPipeDepth {
-    static constexpr int value = MT == 0 ? 4 : (V >= 2 ? 4 : 8);
+    static constexpr int value = MT == 0 ? (DEC ? 1 : 4) : (V >= 2 ? 4 : 8);
 };
 
 template <int V, int PD, class Reader>
@@ -442,6 +444,10 @@ struct RowPipe {
     // slot = i % PD, a constant of the unrolled walk
     __device__ void take(int i, int slot, int L, float* x)
     {
+        if (PD == 1) {
+            rd.next(x);
+            return;
+        }
 #pragma unroll
         for (int v = 0; v < V; ++v) x[v] = ring[slot][v];
         if (i + PD < L) rd.next(ring[slot]);
@@ -470,9 +476,9 @@ __device__ __forceinline__ void walk_uniform_any(Reader& rd, Writer& wr, const i
     int r = -N - 3;                       // frame row of the next value
     rd.seek(r);
     rd.next(xm2); rd.next(xm1); rd.next(x0); rd.next(xp1); rd.next(xp2);
-    constexpr int PD = RowPipeDepth<V, 0>::value;
+    constexpr int PD = RowPipeDepth<V, 0, Reader::decodes>::value;
     RowPipe<V, PD, Reader> pipe(rd);
-    pipe.prime(M);
+    if (PD > 1) pipe.prime(M);
     if (!periodic) {
         // rows already in the window that lie past the upper face
         auto past = [&](int row) { return row >= M - N && row < M; };
@@ -793,9 +799,9 @@ __device__ __forceinline__ void walk_mixed_any(Reader& rd, Writer& wr, const int
     float c1[V], c2[V], k0[V], k1[V], k2[V];
     rd.seek(-Ns - 3);
     rd.next(xm2); rd.next(xm1); rd.next(x0); rd.next(xp1); rd.next(xp2); rd.next(xp3);
-    constexpr int PD = RowPipeDepth<V, 0>::value;
+    constexpr int PD = RowPipeDepth<V, 0, Reader::decodes>::value;
     RowPipe<V, PD, Reader> pipe(rd);
-    pipe.prime(M);
+    if (PD > 1) pipe.prime(M);
     // flux through (j0-1)+1/2, then slide
 #pragma unroll
     for (int v = 0; v < V; ++v) {

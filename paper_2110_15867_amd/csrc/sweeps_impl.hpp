@@ -335,6 +335,16 @@ __global__ void __launch_bounds__(NT) k_vel_uz(const typename Codec<P>::T* __res
     }
 }
 
+// Codes of a contiguous line times its scale.
+template <int P>
+struct ScaledLineReader {
+    static constexpr bool decodes = true;
+    GlobalReader<P, 1, false> g;
+    float sc;
+    __device__ void seek(int r) { g.seek(r); }
+    __device__ void next(float* x) { g.next(x); x[0] *= sc; }
+};
+
 // Fallback for line lengths without a tiled kernel: one thread per contiguous
 // line straight from global memory (two passes for scaled storage).
 template <int P>
@@ -358,18 +368,12 @@ __global__ void __launch_bounds__(256) k_vel_uz_generic(const typename Codec<P>:
         float inv = 1.0f;
         if (Codec<P>::scaled) {
             // pass 1: the output scale
-            struct ScaledReader {
-                GlobalReader<P, 1, false> g;
-                float sc;
-                __device__ void seek(int r) { g.seek(r); }
-                __device__ void next(float* x) { g.next(x); x[0] *= sc; }
-            };
-            ScaledReader srd{rd, sc};
+            ScaledLineReader<P> srd{rd, sc};
             MaxWriter mw{0.0f};
             walk_uniform<1, 0, true>(srd, mw, M, sh, a.periodic, &ofl);
             inv = inv_scale(mw.m);
             sout[line] = mw.m;
-            ScaledReader srd2{rd, sc};
+            ScaledLineReader<P> srd2{rd, sc};
             ContigWriter<P> cw{fout + line * M, M, dir, inv};
             walk_uniform<1, 0, true>(srd2, cw, M, sh, a.periodic, &ofl);
         } else {
