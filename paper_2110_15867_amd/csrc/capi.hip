@@ -367,9 +367,7 @@ int run_kick(const vlasov_grid* g, const Dims& d, int prec, int vbc, const void*
         float* ms = midf != nullptr ? mids : sout;
         int rc = run_velocity(g, d, 0, prec, vbc, fin, sin, mf, ms, field, dt, outflow, st);
         if (rc) return rc;
-        rc = from_hip(launch_kick_yz64(prec, mf, ms, fout, sout, a, shifts, st));
-        if (rc || rho == nullptr) return rc;
-        return run_moments(g, d, prec, fout, sout, rho, umean, nullptr, st);
+        return from_hip(launch_kick_yz64(prec, mf, ms, fout, sout, a, shifts, st));
     }
     if (midf == nullptr) return VLASOV_ERR_WORKSPACE;
     int rc = run_velocity(g, d, 0, prec, vbc, fin, sin, fout, sout, field, dt, outflow, st);
