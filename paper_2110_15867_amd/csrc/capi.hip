@@ -201,6 +201,39 @@ int run_position(const vlasov_grid* g, const Dims& d, int axis, int prec, const 
     return from_hip(launch_position(prec, fin, sin, fout, sout, a, st));
 }
 
+size_t lds_limit()
+{
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+        return 0;
+    return (size_t)v;
+}
+
+// Shift arguments of the drift along an axis; false where its shifts are not
+// finite (the single sweeps' error to report) or its table is too long.
+bool drift_axis(const vlasov_grid* g, const Dims& d, int k, double dta, DriftAxis& x)
+{
+    if (d.nu[k] > kMaxShiftTable) return false;
+    x.n = (int)d.n[k];
+    x.nu = (int)d.nu[k];
+    x.umax = g->umax[k];
+    x.du = 2.0 * g->umax[k] / g->nu[k];
+    x.factor = dta / (g->L[k] / g->n[k]);
+    return isfinite(position_shift(g, k, 0, dta)) &&
+           isfinite(position_shift(g, k, d.nu[k] - 1, dta));
+}
+
+// Arguments of the three drifts in one launch, where a small mesh lets them
+// run so (FP32 storage).
+bool fuse_small_drifts(const vlasov_grid* g, const Dims& d, int prec, double dta, DriftAxis (&ax)[3])
+{
+    if (prec != VLASOV_F32) return false;
+    for (int k = 0; k < 3; ++k)
+        if (!drift_axis(g, d, k, dta, ax[k])) return false;
+    return drift_small_supported(ax, d.Nu, lds_limit());
+}
+
 // Arguments of the fused y and x drifts, where they can run fused: FP32 storage
 // and a shape the kernel takes.  The single drifts are bound by HBM: one pass
 // over f instead of two (64 x 64 x 32 cells of 32^3: 13.8 -> 8.8 ms).
@@ -210,31 +243,23 @@ bool fuse_drifts(const vlasov_grid* g, const Dims& d, int prec, double dta, Drif
 {
     if (prec != VLASOV_F32) return false;
     memset(&a, 0, sizeof(a));
-    DriftAxis* ax[2] = {&a.x, &a.y};
-    for (int k = 0; k < 2; ++k) {
-        if (d.nu[k] > kMaxShiftTable) return false;
-        ax[k]->n = (int)d.n[k];
-        ax[k]->nu = (int)d.nu[k];
-        ax[k]->umax = g->umax[k];
-        ax[k]->du = 2.0 * g->umax[k] / g->nu[k];
-        ax[k]->factor = dta / (g->L[k] / g->n[k]);
-        // (a shift that is not finite is the single sweeps' error to report)
-        if (!isfinite(position_shift(g, k, 0, dta)) ||
-            !isfinite(position_shift(g, k, d.nu[k] - 1, dta)))
-            return false;
-    }
+    if (!drift_axis(g, d, 0, dta, a.x) || !drift_axis(g, d, 1, dta, a.y)) return false;
     a.nz = (int)d.n[2];
     a.nuz = (int)d.nu[2];
     a.Nu = d.Nu;
-    return drift_yx_supported(a);
+    DriftAxis ax[3];
+    return drift_yx_supported(a) && !fuse_small_drifts(g, d, prec, dta, ax);
 }
 
 // The drifts of a step, D_x D_y D_z over dta: z from buffer a to b, then y and
-// x fused from b to c (c may be a; `fa` from fuse_drifts), or y from b to a
-// and x from a to b (fa NULL).
+// x fused from b to c (c may be a; `fa` from fuse_drifts); or (fa NULL) all
+// three from a to b on a small mesh, else y from b to a and x from a to b.
 int run_drifts(const vlasov_grid* g, const Dims& d, int prec, void* a, float* sa, void* b,
                float* sb, void* c, double dta, const DriftArgs* fa, hipStream_t st)
 {
+    DriftAxis ax[3];
+    if (fa == nullptr && fuse_small_drifts(g, d, prec, dta, ax))
+        return from_hip(launch_drift_small((const float*)a, (float*)b, ax, d.Nu, st));
     int rc = run_position(g, d, 2, prec, a, sa, b, sb, dta, st);
     if (rc) return rc;
     if (fa != nullptr) return from_hip(launch_drift_yx((const float*)b, (float*)c, *fa, st));
@@ -282,15 +307,6 @@ int run_velocity(const vlasov_grid* g, const Dims& d, int axis, int prec, int vb
     if (rc) return rc;
     if (axis == 2) return from_hip(launch_vel_uz(prec, fin, sin, fout, sout, a, st));
     return from_hip(launch_vel_strided(prec, fin, sin, fout, sout, a, st));
-}
-
-size_t lds_limit()
-{
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-        return 0;
-    return (size_t)v;
 }
 
 // D_uz D_uy D_ux over dt with one field: fused in LDS where the velocity

@@ -33,13 +33,6 @@ namespace vlasov {
 
 namespace {
 
-// Shift of a position sweep for velocity index j, as the host's table forms it.
-__device__ __forceinline__ double cell_shift(const DriftAxis& x, int j)
-{
-    const double u = -x.umax + ((double)j + 0.5) * x.du;
-    return u * x.factor;
-}
-
 template <int S>
 __global__ void __launch_bounds__(1024) k_drift_yx(const float* __restrict__ fin,
                                                    float* __restrict__ fout, DriftArgs a)

@@ -109,12 +109,23 @@ struct DriftAxis {
     int n, nu;                  // cells along the axis, velocity cells along its velocity axis
     double umax, du, factor;    // s_j = (-umax + (j + 1/2) du) factor, factor = dt a^-2 / dx
 };
+// Shift of a position sweep for velocity index j, as the host's table forms it.
+__device__ __forceinline__ double cell_shift(const DriftAxis& x, int j)
+{
+    const double u = -x.umax + ((double)j + 0.5) * x.du;
+    return u * x.factor;
+}
 struct DriftArgs {
     DriftAxis x, y;
     int nz, nuz;
     long Nu;
     int W, zi, jchunks;         // lanes of a wave (set by the launcher): W u_z values of zi z cells
 };
+// x, y and z drifts of small meshes in one launch (FP32 storage;
+// drift_small.hip); ax: x, y, z
+bool drift_small_supported(const DriftAxis (&ax)[3], long Nu, size_t lds_limit);
+hipError_t launch_drift_small(const float* fin, float* fout, const DriftAxis (&ax)[3], long Nu,
+                              hipStream_t st);
 bool drift_yx_supported(const DriftArgs& a);
 hipError_t launch_drift_yx(const float* fin, float* fout, DriftArgs a, hipStream_t st);
 
