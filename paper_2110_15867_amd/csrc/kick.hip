@@ -13,8 +13,8 @@
 // lives in HBM), which saves the two intermediate roundings the separate
 // sweeps make -- the fused result is the more accurate one.
 //
-// The work-groups are persistent (as many as fit on the chip, each walking
-// cells blockIdx.x, blockIdx.x + gridDim.x, ...).  While one block is swept
+// For 32^3 blocks the work-groups are persistent (as many as fit on the chip,
+// each walking cells blockIdx.x, blockIdx.x + gridDim.x, ...).  While one block is swept
 // in LDS, the next one is already on its way from HBM into registers, and the
 // finished block's stores drain behind the next block's arithmetic: the LDS
 // holds one block, so this is the only way its HBM traffic overlaps compute.
@@ -47,6 +47,14 @@
 #include "sl_mpp5.hpp"
 
 namespace vlasov {
+
+// Whether work-groups of the kick walk several cells.  A 32^3 block has its CU
+// to itself, so only a persistent work-group overlaps a block's HBM traffic
+// with another's arithmetic.  Of 16^3 blocks six or seven share a CU and do
+// that for each other; there persistent work-groups all start a round at once
+// and leave the last one ragged (32 x 32 x 16 cells of 16^3: FP32 142 -> 120 us
+// per kick with a work-group per cell, FP16 135 -> 120).
+constexpr bool kick_persistent(int NU) { return NU > 16; }
 
 // The block in LDS: uz-lines of NU values, LS floats apart.
 template <int P, int NU>
@@ -391,6 +399,8 @@ __global__ void __launch_bounds__(NU * NU) k_kick(const typename Codec<P>::T* __
 
     // FP32: the lines along ux in registers (see above); else the block's slots
     constexpr bool DIRECT = !Codec<P>::scaled;
+    // whether a work-group goes on to further cells (see launch_kick_t)
+    constexpr bool PERSIST = kick_persistent(NU);
     Slots R;
     float xr[DIRECT ? NU : 1];
     float g[3], gn[3];      // field of the cell in hand, and (DIRECT) of the next
@@ -412,9 +422,9 @@ __global__ void __launch_bounds__(NU * NU) k_kick(const typename Codec<P>::T* __
     };
     request(cell);
     arrive();
-    int next = uniform_sgpr(cell + (int)gridDim.x);
+    int next = PERSIST ? uniform_sgpr(cell + (int)gridDim.x) : 0;
     if constexpr (!DIRECT) {
-        if (next < ncell) request(next);
+        if (PERSIST && next < ncell) request(next);
         __syncthreads();
     }
 
@@ -440,7 +450,7 @@ __global__ void __launch_bounds__(NU * NU) k_kick(const typename Codec<P>::T* __
                 float* line = lds + (tf / NU) * LS + tf % NU;
                 o[0] = neg ? kick_regs<NU, NU * LS, PER, true>(line, xr, sh, N)
                            : kick_regs<NU, NU * LS, PER, false>(line, xr, sh, N);
-                if (next < ncell) request(next);
+                if (PERSIST && next < ncell) request(next);
             } else {
                 o[0] = neg ? kick_sweep<P, NU, PER, 0, true>(lds, sh, N, fresh_tid(), nullptr, nullptr)
                            : kick_sweep<P, NU, PER, 0, false>(lds, sh, N, fresh_tid(), nullptr, nullptr);
@@ -520,7 +530,7 @@ __global__ void __launch_bounds__(NU * NU) k_kick(const typename Codec<P>::T* __
             }
             mcell = cell;
         }
-        if (next >= ncell) break;
+        if (!PERSIST || next >= ncell) break;
         arrive();
         cell = next;
         next = uniform_sgpr(cell + (int)gridDim.x);
@@ -995,7 +1005,7 @@ static hipError_t launch_kick_t(const void* fin, const float* sin, void* fout, f
                                                           N * N, lds)) != hipSuccess)
         return e;
     long grid = (long)cus * (per_cu > 0 ? per_cu : 1);
-    if (grid > a.cells) grid = a.cells;
+    if (!kick_persistent(N) || grid > a.cells) grid = a.cells;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(N * N), lds, st, (const T*)fin, sin,
                        (T*)fout, sout, a, tab);
     return hipGetLastError();
