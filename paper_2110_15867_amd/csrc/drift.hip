@@ -42,6 +42,11 @@ __global__ void __launch_bounds__(1024) k_drift_yx(const float* __restrict__ fin
     const int seg = uniform_sgpr((int)(threadIdx.x >> 6));
     // work-group -> (z group, u_z chunk, u_x, u_y), u_y fastest
     int b = blockIdx.x;
+    if (a.pair) {
+        // work-groups go to the eight XCDs in turn: b and b + 8 take the pair
+        const int s = b >> 3;
+        b = 2 * ((s >> 1) * 8 + (b & 7)) + (s & 1);
+    }
     const int jy = b % a.y.nu;
     b /= a.y.nu;
     const int jx = b % a.x.nu;
@@ -208,6 +213,9 @@ hipError_t launch_drift_yx(const float* fin, float* fout, DriftArgs a, hipStream
     const int S = segment_cells(a.y.n);
     const unsigned nt = 64u * (unsigned)((a.y.n + S - 1) / S);
     const unsigned grid = (unsigned)((a.nz + a.zi - 1) / a.zi) * a.jchunks * a.x.nu * a.y.nu;
+    // uz-lines of 16 values are half a cache line; its other half is the next
+    // u_y's, fetched again if that runs under another L2
+    a.pair = a.nuz == 16 && a.y.nu % 2 == 0 && grid % 16 == 0;
     const size_t lds = (size_t)5 * S * nt * sizeof(float);
 #define VL_DRIFT(SV)                                                                            \
     {                                                                                           \

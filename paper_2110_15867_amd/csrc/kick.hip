@@ -231,6 +231,21 @@ __device__ __forceinline__ LineShift kick_shift(const KickArgs& a, const KickShi
     return sh;
 }
 
+// What kick_shift reads back of the shift of (cell, axis).
+__device__ __forceinline__ KickShift packed_shift(const KickArgs& a, long cell, int axis)
+{
+    const LineShift sh = split_shift((double)a.g[(long)axis * a.cells + cell] * a.factor[axis],
+                                     a.nu[axis], a.periodic);
+    KickShift e;
+    e.N = sh.N;
+    e.flags = (sh.neg ? 1 : 0) | (sh.comp ? 2 : 0);
+    e.mu = sh.mu;
+    e.v0 = sh.v0; e.v1 = sh.v1; e.v2 = sh.v2; e.v3 = sh.v3;
+    e.alpha = sh.alpha; e.q = sh.q; e.alpha_c = sh.alpha_c; e.muc = sh.muc;
+    e.pad = 0.0f;
+    return e;
+}
+
 // Sweep of a line whose values are in x in physical order: the result goes to
 // LDS, value p to line[p * S].
 template <int M, int S, bool PER, bool NEG>
@@ -421,12 +436,22 @@ __global__ void __launch_bounds__(NU * NU) k_kick(const typename Codec<P>::T* __
         if constexpr (!DIRECT) R.put(lds, fresh_tid());
     };
     request(cell);
+    // a work-group per cell splits the cell's shifts itself, in three lanes
+    // while its block arrives: a launch less
+    __shared__ KickShift own[3];
+    if (!PERSIST && t < 3) own[t] = packed_shift(a, cell, t);
     arrive();
     int next = PERSIST ? uniform_sgpr(cell + (int)gridDim.x) : 0;
     if constexpr (!DIRECT) {
         if (PERSIST && next < ncell) request(next);
         __syncthreads();
+    } else if constexpr (!PERSIST) {
+        __syncthreads();
     }
+    auto shift_of = [&](int axis) {
+        if constexpr (PERSIST) return kick_shift<NU, PER>(a, tab, cell, axis, g[axis]);
+        else return uniform_shift(kick_shift<NU, PER>(a, own, 0, axis, 0.0f));
+    };
 
     const bool ofl = a.outflow != nullptr && !PER;
     const bool mom = a.rho != nullptr;
@@ -440,7 +465,7 @@ __global__ void __launch_bounds__(NU * NU) k_kick(const typename Codec<P>::T* __
         if (ofl && t == 0) prev = a.outflow[cell];
         float o[3];
         {
-            const LineShift sh = kick_shift<NU, PER>(a, tab, cell, 0, g[0]);
+            const LineShift sh = shift_of(0);
             const int N = uniform_sgpr(sh.N);
             const bool neg = uniform_sgpr(sh.neg ? 1 : 0) != 0;
             if constexpr (DIRECT) {
@@ -458,7 +483,7 @@ __global__ void __launch_bounds__(NU * NU) k_kick(const typename Codec<P>::T* __
         }
         __syncthreads();
         {
-            const LineShift sh = kick_shift<NU, PER>(a, tab, cell, 1, g[1]);
+            const LineShift sh = shift_of(1);
             const int N = uniform_sgpr(sh.N);
             o[1] = uniform_sgpr(sh.neg ? 1 : 0)
                        ? kick_sweep<P, NU, PER, 1, true>(lds, sh, N, fresh_tid(), nullptr, nullptr)
@@ -466,7 +491,7 @@ __global__ void __launch_bounds__(NU * NU) k_kick(const typename Codec<P>::T* __
         }
         __syncthreads();
         {
-            const LineShift sh = kick_shift<NU, PER>(a, tab, cell, 2, g[2]);
+            const LineShift sh = shift_of(2);
             const int N = uniform_sgpr(sh.N);
             float* sl = Codec<P>::scaled ? sout + (long)cell * NL : nullptr;
             o[2] = uniform_sgpr(sh.neg ? 1 : 0)
@@ -550,16 +575,7 @@ __global__ void __launch_bounds__(256) k_kick_shifts(KickArgs a, KickShift* __re
     if (i >= 3 * a.cells) return;
     const long cell = i / 3;
     const int axis = (int)(i - cell * 3);
-    const LineShift sh = split_shift((double)a.g[(long)axis * a.cells + cell] * a.factor[axis],
-                                     a.nu[axis], a.periodic);
-    KickShift e;
-    e.N = sh.N;
-    e.flags = (sh.neg ? 1 : 0) | (sh.comp ? 2 : 0);
-    e.mu = sh.mu;
-    e.v0 = sh.v0; e.v1 = sh.v1; e.v2 = sh.v2; e.v3 = sh.v3;
-    e.alpha = sh.alpha; e.q = sh.q; e.alpha_c = sh.alpha_c; e.muc = sh.muc;
-    e.pad = 0.0f;
-    tab[i] = e;
+    tab[i] = packed_shift(a, cell, axis);
 }
 
 // ---------------------------------------------------------------------------
@@ -1036,7 +1052,7 @@ hipError_t launch_kick(int prec, const void* fin, const float* sin, void* fout, 
 {
     if (a.cells == 0) return hipSuccess;
     if (a.cells > 0x7fffffffL) return hipErrorInvalidValue;   // cell indices are int
-    if (shifts != nullptr) {
+    if (shifts != nullptr && kick_persistent(a.nu[0])) {
         const long n = 3 * a.cells;
         hipLaunchKernelGGL(k_kick_shifts, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a,
                            shifts);

@@ -120,6 +120,7 @@ struct DriftArgs {
     int nz, nuz;
     long Nu;
     int W, zi, jchunks;         // lanes of a wave (set by the launcher): W u_z values of zi z cells
+    int pair;                   // neighbouring work-groups share cache lines: same XCD
 };
 // x, y and z drifts of small meshes in one launch (FP32 storage;
 // drift_small.hip); ax: x, y, z
