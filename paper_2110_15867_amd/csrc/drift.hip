@@ -210,9 +210,13 @@ hipError_t launch_drift_yx(const float* fin, float* fout, DriftArgs a, hipStream
     a.W = a.nuz < 64 ? a.nuz : 64;
     a.zi = a.W < 64 ? 64 / a.W : 1;
     a.jchunks = (a.nuz + 63) / 64;
-    const int S = segment_cells(a.y.n);
-    const unsigned nt = 64u * (unsigned)((a.y.n + S - 1) / S);
     const unsigned grid = (unsigned)((a.nz + a.zi - 1) / a.zi) * a.jchunks * a.x.nu * a.y.nu;
+    int S = segment_cells(a.y.n);
+    // below four waves per SIMD the walk waits on its loads: more, shorter
+    // segments are worth their interfaces (16^3 cells of 16^3, 2048 waves at
+    // S = 8, 4096 at 5: 63 -> 54 us)
+    if ((double)grid * ((a.y.n + S - 1) / S) < 4096.0 && a.y.n <= 80) S = 5;
+    const unsigned nt = 64u * (unsigned)((a.y.n + S - 1) / S);
     // uz-lines of 16 values are half a cache line; its other half is the next
     // u_y's, fetched again if that runs under another L2
     a.pair = a.nuz == 16 && a.y.nu % 2 == 0 && grid % 16 == 0;

@@ -23,6 +23,9 @@ SHAPES = [((9, 8, 8), (32, 32, 16)), ((8, 9, 4), (32, 32, 16)), ((13, 10, 4), (1
           ((10, 12, 4), (32, 32, 32)), ((11, 14, 2), (16, 32, 64)), ((8, 15, 5), (32, 32, 16)),
           ((12, 33, 2), (16, 32, 32)), ((64, 8, 2), (32, 64, 64)), ((9, 128, 1), (8, 16, 64)),
           ((8, 16, 2), (16, 16, 128)),
+          # segments of 5 cells below 4096 waves; the same lines above
+          ((9, 8, 8), (64, 32, 16)), ((10, 12, 4), (64, 32, 32)), ((11, 14, 2), (32, 64, 64)),
+          ((8, 15, 5), (64, 32, 16)), ((8, 16, 2), (32, 16, 128)), ((8, 80, 1), (8, 16, 64)),
           # left to the single sweeps
           ((8, 129, 1), (8, 16, 64)), ((7, 16, 4), (32, 32, 16)), ((16, 7, 8), (32, 32, 16)),
           ((8, 16, 4), (32, 32, 8)), ((8, 16, 4), (3, 5, 16))]
