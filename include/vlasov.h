@@ -214,8 +214,8 @@ size_t vlasov_steps_workspace_bytes(const vlasov_grid* grid, vlasov_prec prec);
  * exact arithmetic the two forms agree):
  *   K(dt/2; g_0), then for k = 0 .. nsteps-1: D_x D_y D_z(dt a2inv[k]) and
  *   K(dt; g_{k+1}), the last one K(dt/2; g_nsteps).
- * nsteps + 1 kicks instead of 2 nsteps: 4 passes over f per step instead of
- * 5.  The semi-Lagrangian flux of one kick over dt is not the composition of
+ * nsteps + 1 kicks instead of 2 nsteps: one pass over f less per step.  The
+ * semi-Lagrangian flux of one kick over dt is not the composition of
  * two over dt/2, so results differ from repeated vlasov_step at the scheme's
  * truncation error; they follow the same merged composition of the single
  * sweeps.  For callers that need no state between the steps.
