@@ -25,7 +25,7 @@ struct PosArgs {
     int us;          // every wave's lanes share one shift and rows hold whole waves (1)
     int ug;          // y sweep: waves can be gathered across u_x so that they share u_y
                      // (the number of uz-lines per wave, each from its own u_x row), or
-                     // 0; used with FP32 storage
+                     // 0; FP16/BF16: where nuz >= 64
     int mix;         // some wave holds lanes that move in both directions (1)
     double shift[kMaxShiftTable];   // s_j = u_j dt a^-2 / dx per velocity index
 };
@@ -48,9 +48,9 @@ struct VelArgs {
 
 hipError_t launch_position(int prec, const void* fin, const float* sin, void* fout, float* sout,
                            const PosArgs& a, hipStream_t st);
-// z sweep through LDS tiles of whole z-lines (zdrift.hip)
-bool z_tiles_supported(const PosArgs& a);
-hipError_t launch_z_tiles(int prec, const void* fin, const float* sin, void* fout, float* sout,
+// z and y sweeps through LDS tiles of whole lines (line_tiles.hip)
+bool line_tiles_supported(int prec, const PosArgs& a);
+hipError_t launch_line_tiles(int prec, const void* fin, const float* sin, void* fout, float* sout,
                           const PosArgs& a, hipStream_t st);
 hipError_t launch_vel_strided(int prec, const void* fin, const float* sin, void* fout, float* sout,
                               const VelArgs& a, hipStream_t st);

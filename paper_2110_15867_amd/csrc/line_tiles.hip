@@ -1,12 +1,13 @@
-// z sweep of lines whose integer shifts differ from lane to lane, through LDS
-// tiles of whole z-lines.
+// z and y sweeps of lines whose integer shifts differ from lane to lane,
+// through LDS tiles of whole lines.
 //
-// The shift follows the contiguous u_z index, so the lanes of a wave move in
-// both directions and, beyond a Courant number of one, by different whole
-// cells.  Walking straight from HBM (k_position) every lane then needs its own
-// row addresses (64-bit arithmetic per row and lane, for the scales too) and a
-// six-cell window with both stencils to pick from: 66 (FP32) to 90 (BF16)
-// vector instructions per cell, which bound it.  Here a wave loads the tile of its 64
+// A z shift follows the contiguous u_z index (a y shift the u_y one, of which a
+// wave holds several), so the lanes of a wave move in both directions and,
+// beyond a Courant number of one, by different whole cells.  Walking straight
+// from HBM (k_position) every lane then needs its own row addresses (64-bit
+// arithmetic per row and lane, for the scales too) and a six-cell window with
+// both stencils to pick from: 66 (FP32) to 90 (BF16) vector instructions per
+// cell, which bound it.  Here a wave loads the tile of its 64
 // lanes (M rows of 64 values, 16-byte accesses, each row and scale read once),
 // and every lane walks its own line out of LDS in its own upwind frame: a row
 // costs one LDS read and two integer instructions, whatever the shift, and the
@@ -78,7 +79,7 @@ __device__ __forceinline__ void wave_fence()
 }
 
 template <int P, int M, int NUZ>
-__global__ void __launch_bounds__(256) k_z_tiles(const typename Codec<P>::T* __restrict__ fin,
+__global__ void __launch_bounds__(256) k_line_tiles(const typename Codec<P>::T* __restrict__ fin,
                                                  const float* __restrict__ sin,
                                                  typename Codec<P>::T* __restrict__ fout,
                                                  float* __restrict__ sout, PosArgs a)
@@ -120,7 +121,10 @@ __global__ void __launch_bounds__(256) k_z_tiles(const typename Codec<P>::T* __r
             *reinterpret_cast<float4*>(tile + (4 * g + rr) * ROW + 16 * c) = v;
         }
     }
-    const LineShift sh = split_shift(a.shift[lane % NUZ], M, true);   // (k0 is a multiple of 64)
+    // z: the shift follows the u_z index (k0 is a multiple of 64); y: the uz-line's u_y
+    const int j = a.pst == 1 ? lane % NUZ
+                             : (int)(((unsigned)(k0 / NUZ % a.nshift) + lane / NUZ) % (unsigned)a.nshift);
+    const LineShift sh = split_shift(a.shift[j], M, true);
     const LaneLine l = lane_line(sh);
     wave_fence();
 
@@ -192,8 +196,8 @@ hipError_t launch_m(const void* fin, const float* sin, void* fout, float* sout, 
 {
     using T = typename Codec<P>::T;
     const unsigned blocks = (unsigned)((a.O * (a.I / 64) + 3) / 4);
-    auto kern = a.nuz == 16 ? k_z_tiles<P, M, 16>
-                            : (a.nuz == 32 ? k_z_tiles<P, M, 32> : k_z_tiles<P, M, 64>);
+    auto kern = a.nuz == 16 ? k_line_tiles<P, M, 16>
+                            : (a.nuz == 32 ? k_line_tiles<P, M, 32> : k_line_tiles<P, M, 64>);
     hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), 0, st, (const T*)fin, sin, (T*)fout, sout, a);
     return hipGetLastError();
 }
@@ -211,27 +215,38 @@ hipError_t launch_p(const void* fin, const float* sin, void* fout, float* sout, 
 
 }  // namespace
 
-// z sweeps (the shift follows u_z) of compiled line lengths whose rows hold
-// whole waves of whole uz-lines.  Lines of 16 and 32 cells: always (32^3 cells
-// of 32^3 with shifts up to 2.5 cells: FP32 1.89 -> 1.43 ms, BF16 2.58 ->
-// 1.36; 64 x 64 x 32 cells with shifts below one: FP32 6.04 -> 5.89 ms, FP16,
-// the paired walk, 6.58 -> 5.16).  Lines of 64 cells, whose tiles leave two
-// waves per SIMD: where some line moves by a cell or more (16 x 16 x 64 cells
-// of 32^3 with 2.5: FP32 1.07 -> 0.89 ms, FP16 1.13 -> 0.88; with 0.3: FP32
-// 0.77 from HBM, 0.90 from tiles, FP16 0.79 and 0.85).
-bool z_tiles_supported(const PosArgs& a)
+// z sweeps (the shift follows u_z) and y sweeps (u_y) of compiled line lengths
+// whose rows hold whole waves of whole uz-lines.  z, lines of 16 and 32 cells:
+// always (32^3 cells of 32^3 with shifts up to 2.5 cells: FP32 1.89 -> 1.43 ms,
+// BF16 2.58 -> 1.36; 64 x 64 x 32 cells with shifts below one: FP32 6.04 ->
+// 5.89 ms, FP16, the paired walk, 6.58 -> 5.16).  Lines of 64 cells, whose
+// tiles leave two waves per SIMD: where some line moves by a cell or more
+// (16 x 16 x 64 cells of 32^3 with 2.5: FP32 1.07 -> 0.89 ms, FP16 1.13 -> 0.88;
+// with 0.3: FP32 0.77 from HBM, 0.90 from tiles, FP16 0.79 and 0.85).
+//
+// y, uz-lines of 16 values: always.  A wave of k_position that shares one u_y
+// reads pieces of 64 bytes or less, and one of consecutive elements holds 16
+// values of u_y (32^3 cells of 16^3: FP32 333 -> 223 us, FP16 with shifts up to
+// 2.5 cells 630 -> 176, 0.3 271 -> 161; 64^3 cells FP32 2.84 -> 1.83 ms).
+// uz-lines of 32 values: FP16/BF16 lines of 16 and 32 cells where some line
+// moves by a cell or more, so that the lanes of a wave read different rows
+// (32^3 cells of 32^3, FP16: 2.5 cells 1.80 -> 1.36 ms, 0.3 cells 1.27 from HBM
+// and 1.36 from tiles; lines of 64 cells 4.9 and 6.3 ms; FP32 1.68 and 1.91).
+bool line_tiles_supported(int prec, const PosArgs& a)
 {
-    if (a.pst != 1 || a.nshift != a.nuz || a.V != 1) return false;
+    const bool z = a.pst == 1 && a.nshift == a.nuz && a.V == 1;
+    if (!z && a.pst != a.nuz) return false;
     if (a.nuz != 16 && a.nuz != 32 && a.nuz != 64) return false;
     if (a.M != 16 && a.M != 32 && a.M != 64) return false;
     if (a.I % 64 != 0 || a.O * (a.I / 64) > 4 * 0x7fffffffL) return false;
-    if (a.M != 64) return true;
+    if (z ? a.M != 64 : a.nuz == 16) return true;
+    if (!z && (a.nuz != 32 || a.M == 64 || prec == PREC_F32)) return false;
     for (int j = 0; j < a.nshift; ++j)
         if (fabs(a.shift[j]) >= 1.0) return true;
     return false;
 }
 
-hipError_t launch_z_tiles(int prec, const void* fin, const float* sin, void* fout, float* sout,
+hipError_t launch_line_tiles(int prec, const void* fin, const float* sin, void* fout, float* sout,
                           const PosArgs& a, hipStream_t st)
 {
     if (a.O * a.I == 0) return hipSuccess;

@@ -19,7 +19,7 @@ VL_DECL(launch_vel_uz, VelArgs)
 hipError_t launch_position(int prec, const void* fin, const float* sin, void* fout, float* sout,
                            const PosArgs& a, hipStream_t st)
 {
-    if (z_tiles_supported(a)) return launch_z_tiles(prec, fin, sin, fout, sout, a, st);
+    if (line_tiles_supported(prec, a)) return launch_line_tiles(prec, fin, sin, fout, sout, a, st);
     switch (prec) {
         case PREC_F16: return launch_position_f16(fin, sin, fout, sout, a, st);
         case PREC_BF16: return launch_position_bf16(fin, sin, fout, sout, a, st);

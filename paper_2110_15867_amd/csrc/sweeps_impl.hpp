@@ -57,7 +57,7 @@ __global__ void __launch_bounds__(256, 4) k_position(const typename Codec<P>::T*
     long o = t / IV;
     long k = (t - o * IV) * V;
     long k0w = 0;                                  // gathered mapping: lane 0's element
-    const bool gathered = !Codec<P>::scaled && a.ug > 0;
+    const bool gathered = a.ug > 0 && (!Codec<P>::scaled || a.nuz >= 64);
     if constexpr (US) {
         if (gathered) {
             // Gathered mapping (y sweep).  A wave holds R = a.ug uz-lines,
@@ -424,7 +424,7 @@ inline hipError_t launch_position_v(const void* fin, const float* sin, void* fou
     // the line constants in scalar registers; where no wave holds lanes of
     // both directions (y sweeps of the usual blocks) the mixed walk is left
     // out, which frees registers
-    const bool us = (a.us != 0 || (a.ug > 0 && !Codec<P>::scaled)) && V == 4;
+    const bool us = (a.us != 0 || (a.ug > 0 && (!Codec<P>::scaled || a.nuz >= 64))) && V == 4;
     const bool mix = a.mix != 0 || V != 4;
 #define VL_POS(MTV) \
     if (us && g32) hipLaunchKernelGGL((k_position<P, V, MTV, G32, true, false>), dim3(blocks), dim3(256), 0, st, (const T*)fin, sin, (T*)fout, sout, a); \
