@@ -71,13 +71,6 @@ __device__ __forceinline__ float flux_lane(const Stencil& s, const LaneLine& l, 
     return med3(pre, 0.0f, s.c);
 }
 
-__device__ __forceinline__ void wave_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 template <int P, int M, int NUZ>
 __global__ void __launch_bounds__(256) k_line_tiles(const typename Codec<P>::T* __restrict__ fin,
                                                  const float* __restrict__ sin,

@@ -11,6 +11,15 @@
 
 namespace vlasov {
 
+// Orders a wave's LDS accesses before those after it, for tiles that belong to
+// one wave.
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ---------------------------------------------------------------------------
 // Row readers and writers
 // ---------------------------------------------------------------------------
