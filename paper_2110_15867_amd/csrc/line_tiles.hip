@@ -171,8 +171,11 @@ __global__ void __launch_bounds__(256) k_line_tiles(const typename Codec<P>::T* 
         const float x[4] = {v.x, v.y, v.z, v.w};
         float inv = 1.0f;
         if (Codec<P>::scaled) {
-            const float m = group_max_nonneg<G>(
-                fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3]))));
+            // from 0, as the other writers: a NaN never becomes the scale of its line
+            float m = 0.0f;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) m = fmaxf(m, fabsf(x[u]));
+            m = group_max_nonneg<G>(m);
             inv = inv_scale(m);
             if (c % G == 0) sout[s0 + 4 * g * sI + soff] = m;
         }

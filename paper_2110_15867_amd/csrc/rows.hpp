@@ -376,7 +376,8 @@ struct PairRowWriter {
         const __amdgpu_buffer_rsrc_t rs = row_rsrc(base + (long)i * stride, nbytes);
         Pack<T, 2> q;
         if (Codec<P>::scaled) {
-            float m = fmaxf(fabsf(xa), fabsf(xb));
+            // (from 0: a NaN never becomes the scale of its line)
+            float m = fmaxf(fmaxf(0.0f, fabsf(xa)), fabsf(xb));
             m = group_max_nonneg<H>(m);
             const float inv = inv_scale(m);
             q.v[0] = quantize<P>(s0, inv);
