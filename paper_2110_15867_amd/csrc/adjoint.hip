@@ -843,7 +843,9 @@ __global__ void __launch_bounds__(256) k_velocity_adj(const float* __restrict__ 
     const long cell0 = (long)blockIdx.x * cpg;
     const int nc = (int)(a.cells - cell0 < cpg ? a.cells - cell0 : cpg);
     adj_entries(tab, a, cell0, nc);
-    const int I = (int)a.I, lpc = (int)(a.nsub * a.I);    // within a velocity block
+    // within a velocity block, at most 2^31 - 1 (unsigned: a counter passes its
+    // bound by up to a work-group)
+    const unsigned I = (unsigned)a.I, lpc = (unsigned)(a.nsub * a.I);
     for (int c = 0; c < nc; ++c) {
         const long cell = cell0 + c;
         const LineShift sh = uniform_shift(tab[c].sh);
@@ -853,8 +855,8 @@ __global__ void __launch_bounds__(256) k_velocity_adj(const float* __restrict__ 
         // frame row 0 of the cell's first line
         const long top = cell * a.nsub * a.M * a.I + (dir > 0 ? 0 : (long)(a.M - 1) * a.I);
         const long step = dir * a.I * (long)sizeof(float);
-        for (int l = threadIdx.x; l < lpc; l += blockDim.x) {
-            const int sub = l / I, k = l - sub * I;
+        for (unsigned l = threadIdx.x; l < lpc; l += blockDim.x) {
+            const unsigned sub = l / I, k = l - sub * I;
             const long off = (long)sub * a.M * I + k;
             const long o0 = FAR ? off : uniform_long(off);   // lane 0's line, the wave's first
             const unsigned lane = (unsigned)((off - o0) * (long)sizeof(float));
