@@ -202,15 +202,6 @@ int run_position(const vlasov_grid* g, const Dims& d, int axis, int prec, const 
     return from_hip(launch_position(prec, fin, sin, fout, sout, a, st));
 }
 
-size_t lds_limit()
-{
-    int dev = 0, v = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
-    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-        return 0;
-    return (size_t)v;
-}
-
 // Shift arguments of the drift along an axis; false where its shifts are not
 // finite (the single sweeps' error to report) or its table is too long.
 bool drift_axis(const vlasov_grid* g, const Dims& d, int k, double dta, DriftAxis& x)
@@ -249,7 +240,7 @@ bool fuse_drifts(const vlasov_grid* g, const Dims& d, int prec, double dta, Drif
     a.nuz = (int)d.nu[2];
     a.Nu = d.Nu;
     DriftAxis ax[3];
-    return drift_yx_supported(a) && !fuse_small_drifts(g, d, prec, dta, ax);
+    return drift_yx_supported(a, lds_limit()) && !fuse_small_drifts(g, d, prec, dta, ax);
 }
 
 // The drifts of a step, D_x D_y D_z over dta: z from buffer a to b, then y and

@@ -181,9 +181,31 @@ int segment_cells(int ny)
 
 }  // namespace
 
+// Work-groups, cells per segment and threads of the fused pass.
+struct DriftShape {
+    double groups;
+    int S, threads;
+    size_t lds() const { return (size_t)5 * S * threads * sizeof(float); }
+};
+
+static DriftShape drift_shape(const DriftArgs& a)
+{
+    DriftShape r;
+    const int zi = a.nuz < 64 ? 64 / a.nuz : 1;
+    r.groups = (double)((a.nz + zi - 1) / zi) * ((a.nuz + 63) / 64) * a.x.nu * a.y.nu;
+    r.S = segment_cells(a.y.n);
+    // below four waves per SIMD the walk waits on its loads: more, shorter
+    // segments are worth their interfaces (16^3 cells of 16^3, 2048 waves at
+    // S = 8, 4096 at 5: 63 -> 54 us)
+    if (r.groups * ((a.y.n + r.S - 1) / r.S) < 4096.0 && a.y.n <= 80) r.S = 5;
+    r.threads = 64 * ((a.y.n + r.S - 1) / r.S);
+    return r;
+}
+
 // Where the fused pass is taken, besides what its indexing needs (one
 // work-group of at most sixteen segments per y-line, 32-bit offsets inside a
-// plane, lines of at least a segment and its wrap):
+// plane, lines of at least a segment and its wrap, LDS for the closing planes
+// of its threads: 160 KiB for 16 segments of 8):
 //  * u_z lines that fill waves and cache lines (16, 32 or a multiple of 64
 //    values): with 8 the pieces of a row are 32 bytes (48^3 cells of 8^3: step
 //    895 us fused, 801 apart), with 20 four lanes idle and lines straddle
@@ -192,17 +214,15 @@ int segment_cells(int ny)
 //    x-line, so fewer leave it waiting on its own loads (8^3 of 16^3, 512
 //    waves: 77 us, 72 apart; 16^3 of 16^3, 2048 waves: equal; 20^3 of 16^3:
 //    359 us, 392 apart).
-bool drift_yx_supported(const DriftArgs& a)
+bool drift_yx_supported(const DriftArgs& a, size_t lds_limit)
 {
     if (a.x.n < 8 || a.y.n < 8) return false;
     if (a.nuz != 16 && a.nuz != 32 && a.nuz % 64 != 0) return false;
     const int S = segment_cells(a.y.n), segs = (a.y.n + S - 1) / S;
     if (segs > 16) return false;
     if ((double)a.y.n * a.nz * a.Nu * 4.0 >= 4294967296.0) return false;
-    const int zi = a.nuz < 64 ? 64 / a.nuz : 1;
-    const double groups =
-        (double)((a.nz + zi - 1) / zi) * ((a.nuz + 63) / 64) * a.x.nu * a.y.nu;
-    return groups * segs >= 2048.0 && groups < 2147483647.0;
+    const DriftShape r = drift_shape(a);
+    return r.groups * segs >= 2048.0 && r.groups < 2147483647.0 && r.lds() <= lds_limit;
 }
 
 hipError_t launch_drift_yx(const float* fin, float* fout, DriftArgs a, hipStream_t st)
@@ -210,17 +230,12 @@ hipError_t launch_drift_yx(const float* fin, float* fout, DriftArgs a, hipStream
     a.W = a.nuz < 64 ? a.nuz : 64;
     a.zi = a.W < 64 ? 64 / a.W : 1;
     a.jchunks = (a.nuz + 63) / 64;
-    const unsigned grid = (unsigned)((a.nz + a.zi - 1) / a.zi) * a.jchunks * a.x.nu * a.y.nu;
-    int S = segment_cells(a.y.n);
-    // below four waves per SIMD the walk waits on its loads: more, shorter
-    // segments are worth their interfaces (16^3 cells of 16^3, 2048 waves at
-    // S = 8, 4096 at 5: 63 -> 54 us)
-    if ((double)grid * ((a.y.n + S - 1) / S) < 4096.0 && a.y.n <= 80) S = 5;
-    const unsigned nt = 64u * (unsigned)((a.y.n + S - 1) / S);
+    const DriftShape r = drift_shape(a);
+    const unsigned grid = (unsigned)r.groups, nt = (unsigned)r.threads;
     // uz-lines of 16 values are half a cache line; its other half is the next
     // u_y's, fetched again if that runs under another L2
     a.pair = a.nuz == 16 && a.y.nu % 2 == 0 && grid % 16 == 0;
-    const size_t lds = (size_t)5 * S * nt * sizeof(float);
+    const size_t lds = r.lds();
 #define VL_DRIFT(SV)                                                                            \
     {                                                                                           \
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(k_drift_yx<SV>),  \
@@ -229,7 +244,7 @@ hipError_t launch_drift_yx(const float* fin, float* fout, DriftArgs a, hipStream
         if (e != hipSuccess) return e;                                                          \
         hipLaunchKernelGGL(k_drift_yx<SV>, dim3(grid), dim3(nt), lds, st, fin, fout, a);         \
     }
-    switch (S) {
+    switch (r.S) {
         case 5: VL_DRIFT(5) break;
         case 6: VL_DRIFT(6) break;
         case 7: VL_DRIFT(7) break;

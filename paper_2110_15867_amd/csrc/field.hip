@@ -471,6 +471,10 @@ bool make_plan(int n, FftPlan& p)
 }
 
 size_t lds_bytes(int n, int extra) { return ((size_t)2 * n * kLines + n + extra) * sizeof(double2); }
+// of the passes that hold most: x with phi_k beside its lines, z inverse with
+// the half spectra
+size_t lds_x(int n) { return lds_bytes(n, n * kLines); }
+size_t lds_z_inv(int n) { return lds_bytes(n, 2 * kLines * (n / 2 + 1)); }
 
 // two values of a bundle per thread (64 threads at least, 256 at most): the
 // loads, stores and spectral factors of a bundle are short chains, the
@@ -502,8 +506,8 @@ hipError_t launch_field_fft(const double* rho, float* g, const Mesh& a, void* wo
     const int tiles = (nh + kLines - 1) / kLines;
     const int rows = n0 * n1;
     const long rows3 = 3L * rows;
-    const size_t lx = lds_bytes(n0, n0 * kLines), ly = lds_bytes(n1, 0);
-    const size_t lf = lds_bytes(n2, 0), li = lds_bytes(n2, 2 * kLines * nh);
+    const size_t lx = lds_x(n0), ly = lds_bytes(n1, 0);
+    const size_t lf = lds_bytes(n2, 0), li = lds_z_inv(n2);
     hipError_t e;
     if ((e = allow_lds(k_fft_z_fwd, lf)) != hipSuccess) return e;
     if ((e = allow_lds(k_fft_y_fwd, ly)) != hipSuccess) return e;
@@ -524,7 +528,7 @@ hipError_t launch_field_fft(const double* rho, float* g, const Mesh& a, void* wo
 }
 
 // ---------------------------------------------------------------------------
-// Meshes with an axis beyond kMaxLine cells: plain separable DFTs, one output
+// Meshes with an axis beyond kMaxLine cells, or whose lines LDS does not hold: plain separable DFTs, one output
 // element per thread and one axis per pass, with exact twiddle indices
 // (k l mod n).
 // ---------------------------------------------------------------------------
@@ -659,6 +663,12 @@ hipError_t launch_field_direct(const double* rho, float* g, const Mesh& a, void*
 
 }  // namespace
 
+bool field_fft_supported(const int n[3], size_t lds_limit)
+{
+    if (n[0] > kMaxLine || n[1] > kMaxLine || n[2] > kMaxLine) return false;
+    return lds_x(n[0]) <= lds_limit && lds_bytes(n[1], 0) <= lds_limit && lds_z_inv(n[2]) <= lds_limit;
+}
+
 hipError_t launch_field(const double* rho, float* g, const FieldArgs& a, void* work,
                         hipStream_t st)
 {
@@ -670,7 +680,7 @@ hipError_t launch_field(const double* rho, float* g, const FieldArgs& a, void* w
     }
     m.coupling = a.coupling;
     m.cells = a.cells;
-    if (a.n[0] <= kMaxLine && a.n[1] <= kMaxLine && a.n[2] <= kMaxLine)
+    if (field_fft_supported(a.n, lds_limit()))
         return launch_field_fft(rho, g, m, work, st);
     return launch_field_direct(rho, g, m, work, st);
 }

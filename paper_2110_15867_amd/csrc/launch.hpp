@@ -46,6 +46,16 @@ struct VelArgs {
     long cells;
 };
 
+// LDS a work-group of the current device may hold.
+inline size_t lds_limit()
+{
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+        return 0;
+    return (size_t)v;
+}
+
 hipError_t launch_position(int prec, const void* fin, const float* sin, void* fout, float* sout,
                            const PosArgs& a, hipStream_t st);
 // z and y sweeps through LDS tiles of whole lines (line_tiles.hip)
@@ -127,7 +137,7 @@ struct DriftArgs {
 bool drift_small_supported(const DriftAxis (&ax)[3], long Nu, size_t lds_limit);
 hipError_t launch_drift_small(const float* fin, float* fout, const DriftAxis (&ax)[3], long Nu,
                               hipStream_t st);
-bool drift_yx_supported(const DriftArgs& a);
+bool drift_yx_supported(const DriftArgs& a, size_t lds_limit);
 hipError_t launch_drift_yx(const float* fin, float* fout, DriftArgs a, hipStream_t st);
 
 struct MomArgs {
@@ -170,6 +180,8 @@ inline size_t field_workspace_bytes(const int n[3])
     for (int d = 0; d < 3; ++d) b += field_align((size_t)n[d] * 16);
     return b + 2 * field_align(cells * 16) + field_align(3 * cells * 16);
 }
+// whether lines of these lengths are transformed in LDS (else direct sums)
+bool field_fft_supported(const int n[3], size_t lds_limit);
 hipError_t launch_field(const double* rho, float* g, const FieldArgs& a, void* work,
                         hipStream_t st);
 hipError_t launch_moments_adj(const MomArgs& a, const double* lam_rho, const double* lam_umean,
