@@ -53,7 +53,7 @@ __device__ __forceinline__ void drift_any(int M, float* x, int step, const LineS
 __global__ void __launch_bounds__(1024) k_drift_small(const float* __restrict__ fin,
                                                       float* __restrict__ fout, SmallMesh a)
 {
-    extern __shared__ float lds[];
+    extern __shared__ __align__(16) float lds[];
     __shared__ LineShift tab[W + 2];      // of the W u_z values, of u_y and of u_x
     const int nx = a.ax[0].n, ny = a.ax[1].n, nz = a.ax[2].n;
     const int nuy = a.ax[1].nu, nuz = a.ax[2].nu;

@@ -403,7 +403,7 @@ __global__ void __launch_bounds__(NU * NU) k_kick(const typename Codec<P>::T* __
     constexpr int NT = NU * NU;
     constexpr int NL = NU * NU;                 // uz-lines per cell
     constexpr int NV = NU * NU * NU;
-    extern __shared__ float lds[];
+    extern __shared__ __align__(16) float lds[];
     __shared__ double red[3 * (NT / 64)];
     __shared__ double mred[4 * (NT / 64)];       // wave sums of the block's moments
     __shared__ float lmax[Codec<P>::scaled ? NL : 1];   // new uz-line scales
@@ -629,7 +629,7 @@ __global__ void __launch_bounds__(256) k_vel_uz_tiles(const typename Codec<P>::T
     constexpr int NT = Slots::NT;
     constexpr int NTILE = NU * NU / NT;          // tiles per cell
     constexpr int TE = NT * NU;                  // values per tile
-    extern __shared__ float lds[];
+    extern __shared__ __align__(16) float lds[];
     __shared__ float lmax[Codec<P>::scaled ? NT : 1];
     __shared__ double red[NT / 64];
     const int t = threadIdx.x;
@@ -777,7 +777,7 @@ __global__ void __launch_bounds__(512) k_kick_yz64(const typename Codec<P>::T* f
     constexpr int SE = Slots::SE;
     constexpr int NSLAB = NU / SX;
     constexpr long BLK = (long)NU * NU * NU;
-    extern __shared__ float lds[];
+    extern __shared__ __align__(16) float lds[];
     __shared__ float lmax[Codec<P>::scaled ? NT : 1];
     __shared__ double red[2 * (NT / 64)];
     __shared__ double mred[4 * (NT / 64)];      // wave sums of a block's moments

@@ -5,7 +5,9 @@ would request, the rule leaves the call to the general kernels (the launch
 would fail); with enough, it takes it.
 """
 import ctypes
+import glob
 import os
+import re
 
 import pytest
 
@@ -57,3 +59,19 @@ def test_field_transforms_ask_for_their_lds(n, need):
     assert rule(mesh, need)
     assert not rule(mesh, need - 1)
     assert not rule((ctypes.c_int * 3)(257, 8, 8), 160 * KB)
+
+
+def test_arrays_of_16_byte_accesses_are_declared_so():
+    """Dynamic LDS begins behind a kernel's static arrays, at the alignment the
+    array is declared with: 16 bytes in every file that reads or writes it by
+    groups of four floats."""
+    csrc = os.path.join(ROOT, "paper_2110_15867_amd", "csrc")
+    seen = 0
+    for path in sorted(glob.glob(os.path.join(csrc, "*.h*"))):
+        text = open(path).read()
+        arrays = re.findall(r"(?:extern )?__shared__ [^;{]*\b(?:lds)\[[^;]*;", text)
+        if not arrays or not re.search(r"reinterpret_cast<(?:const )?float(?:4|x4)\*>\((?:lds|line|tile|at)\b", text):
+            continue
+        seen += 1
+        assert all("__align__(16)" in a for a in arrays), (os.path.basename(path), arrays)
+    assert seen >= 3        # the kicks, the small meshes' drifts, the line tiles
