@@ -71,8 +71,9 @@ struct BlockSlots {
     using T = typename Codec<P>::T;
     static constexpr int NT = NU * NU;
     static constexpr int NS = NU * NU * NU / (NT * 4);
-    Pack<T, 4> q[NS];
-    float sc[NS];
+    static constexpr int HELD = Codec<P>::scaled ? NS : 1;   // (FP32 lines wait in registers of their own)
+    Pack<T, 4> q[HELD];
+    float sc[HELD];
     float g[3];        // the cell's acceleration field (ux, uy, uz)
 
     // element index of slot s: consecutive threads take consecutive 4-value
@@ -734,8 +735,9 @@ struct SlabSlots {
     static constexpr int SE = SX * NU * NU;        // values per slab
     static constexpr int NS = SE / (NT * 4);       // 4-value groups per thread
     static constexpr int LS = Codec<P>::scaled ? NU + 1 : NU + 4;   // line stride (see KickLds)
-    Pack<T, 4> q[NS];
-    float sc[NS];
+    static constexpr int HELD = Codec<P>::scaled ? NS : 1;   // (FP32 lines wait in registers of their own)
+    Pack<T, 4> q[HELD];
+    float sc[HELD];
     __device__ static int elem(int s, int t) { return (s * NT + t) * 4; }
     // slab k of a block: values k*SE .., uz-lines k*SX*NU ..
     __device__ void load(const T* src, const float* ssrc, int t)

@@ -650,8 +650,7 @@ __device__ __forceinline__ void walk_uniform(Reader& rd, Writer& wr, const int M
         xm2[v] = xm1[v]; xm1[v] = x0[v]; x0[v] = xp1[v]; xp1[v] = xp2[v];
         dm2[v] = dm1[v]; dm1[v] = d0[v]; d0[v] = dp1[v];
     }
-    constexpr int UNR = MT > 0 ? MT : 1;
-#pragma unroll UNR
+#pragma unroll MT
     for (int i = 0; i < M; ++i) {
         // new row j+2 for j = i - N
         if (periodic && i >= M - 5) {
@@ -910,8 +909,7 @@ __device__ __forceinline__ void walk_mixed(Reader& rd, Writer& wr, const int Mrt
         q0[v] = q1[v]; q1[v] = q2[v]; q2[v] = q3[v]; q3[v] = q4[v];
     }
     const float sgn = neg ? -1.0f : 1.0f;
-    constexpr int UNR = MT > 0 ? MT : 1;
-#pragma unroll UNR
+#pragma unroll MT
     for (int i = 0; i < M; ++i) {
         if (i >= M - 6) {
 #pragma unroll
