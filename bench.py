@@ -157,12 +157,14 @@ def timed_run(V, torch, inputs, w, grid, prec, K, W, dev, stream):
     torch.cuda.synchronize()
     _log("bench: inputs ready")
 
-    # Each step is the five launches vlasov_step makes -- kick(g_n) [ux, uy,
-    # uz fused in LDS], z, y, x, kick(g_np1) -- issued through the public
-    # single-launch calls so that HIP events between them time every kernel
-    # inside the timed region itself (no synchronisation until the end).  The
-    # warmup issues the same calls, so no first-call cost lands in the timed
-    # region.
+    # Each step is issued as five public single launches -- kick(g_n) [ux, uy,
+    # uz fused in LDS], z, y, x, kick(g_np1) -- so that HIP events between them
+    # time every kernel inside the timed region itself (no synchronisation
+    # until the end).  The results are vlasov_step's bits; with FP32 storage
+    # vlasov_step makes four launches on this grid, y and x in one pass over f,
+    # and is faster: its own time is the companion "fused_moments", step_ms.
+    # The warmup issues the same calls, so no first-call cost lands in the
+    # timed region.
     names = ["kick", "z", "y", "x", "kick"]
     wf = V.empty_state(grid, prec, dev)
     bufs = [state, out, wf]                # input, and the two ping-pong targets
@@ -536,7 +538,7 @@ def main():
         "config": {"workload": w.name, "nx": list(w.n), "nu": list(w.nu), "L": list(w.L),
                    "dt": w.dt, "sweeps_per_step": 9, "launches_per_step": 5,
                    "storage": args.prec},
-        # the bytes the five launches of a step must move (one read and one
+        # the bytes the step's five single launches must move (one read and one
         # write of f each), over the step time
         "hbm_tbps_algorithmic": step_bytes / (total_ms / K * 1e-3) / 1e12,
         "step_hbm_frac": step_frac,

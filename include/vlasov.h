@@ -157,7 +157,8 @@ int vlasov_advect_uz(const vlasov_grid* grid, vlasov_prec prec, vlasov_vbc vbc,
  * three sweeps in FP32 and round only the result, so they differ from the
  * three single sweeps by those sweeps' two intermediate roundings (about one
  * code unit of the line scale); the outflow tally differs by the same
- * relative amount.  Other shapes give the three sweeps' bits.
+ * relative amount.  Other shapes give the three sweeps' bits of f and scales,
+ * and their outflow up to the order of its FP64 sums.
  */
 int vlasov_kick(const vlasov_grid* grid, vlasov_prec prec, vlasov_vbc vbc, const void* f_in,
                 const float* scale_in, void* f_out, float* scale_out, const float* g, double dt,
@@ -244,7 +245,9 @@ size_t vlasov_field_workspace_bytes(const vlasov_grid* grid);
  *   phi_k = -coupling rho_k / |k|^2 (mean removed), g_a,k = -i k_a phi_k,
  *   k_a = 2 pi m_a / L_a with m_a the signed index; k_a = 0 on the Nyquist
  *   plane of an even axis for the derivative.
- * FP64 throughout (separable DFTs, one pass per axis), g stored as FP32.
+ * FP64 throughout, g stored as FP32.  Five passes over the half spectrum with
+ * the lines transformed in LDS (axes up to 256 cells); longer axes by direct
+ * sums, one pass per axis.
  *   rho      : FP64 device [nx][ny][nz] (e.g. from vlasov_moments)
  *   coupling : 4 pi G a(t)^2
  *   field    : FP32 device [3][nx][ny][nz], the layout vlasov_step takes

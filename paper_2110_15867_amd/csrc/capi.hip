@@ -229,8 +229,10 @@ bool fuse_small_drifts(const vlasov_grid* g, const Dims& d, int prec, double dta
 // Arguments of the fused y and x drifts, where they can run fused: FP32 storage
 // and a shape the kernel takes.  The single drifts are bound by HBM: one pass
 // over f instead of two (64 x 64 x 32 cells of 32^3: 13.8 -> 8.8 ms).
-// FP16/BF16 drifts are bound by their vector arithmetic, which fusing does
-// not reduce.
+// FP16/BF16 drifts stay apart: between the two the y planes would have to be
+// rounded to codes, a line maximum over lanes for each, where the FP32 form
+// hands values on in registers.  (A fused form of theirs has not been built or
+// timed; it would save a decode and an encode per value.)
 bool fuse_drifts(const vlasov_grid* g, const Dims& d, int prec, double dta, DriftArgs& a)
 {
     if (prec != VLASOV_F32) return false;

@@ -163,7 +163,8 @@ hipError_t launch_encode(int prec, const float* f, void* codes, float* scale, lo
 hipError_t launch_decode(int prec, const void* codes, const float* scale, float* f, long total,
                          long nuz, hipStream_t st);
 
-// Field of a density on the periodic mesh (Eq. 2), FP64 DFTs.
+// Field of a density on the periodic mesh (Eq. 2) in FP64: transforms of lines
+// in LDS, or direct sums.
 struct FieldArgs {
     int n[3];
     double L[3];
